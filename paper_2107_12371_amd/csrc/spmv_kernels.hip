@@ -232,6 +232,14 @@ __device__ __forceinline__ int cwin_run_of(const uint2 *run_map, int w) {
 template <typename V, typename X, typename Y, typename A, int NT, int EPI>
 __global__ __launch_bounds__(kBlock) void k_cwin(SpmvArgs<V, X, Y> g) {
     using Regs = typename CwinRegsSel<V, NT>::type;
+    // y of a plain binary64 product is stored non-temporally: its lines leave
+    // the XCD's L2 at once instead of being written back line by line between
+    // the stream's reads (y is 4% of the bytes, but storing it cost 16% of the
+    // time; 16M-row mesh matrix 518 -> 502 us, same bits).
+    // FP32 and BF16 products were no faster with it (4M rows 83.8 -> 85.2 us
+    // and equal), and a solver's y is read again by its next kernel, so those
+    // keep ordinary stores.
+    constexpr bool kNTY = sizeof(V) == sizeof(double);
     __shared__ A buf[Regs::kProd];
     constexpr int kMapWords = Regs::kProd / 32;
     __shared__ int32_t run_x[kCwinMaxRunsDev], run_p[kCwinMaxRunsDev + 1];
@@ -252,7 +260,7 @@ __global__ __launch_bounds__(kBlock) void k_cwin(SpmvArgs<V, X, Y> g) {
         t.gather([x](int c) { return x[c]; }, xv);
         t.products(xv, buf);
         __syncthreads();
-        tile_rows<Y, A, EPI>(pre, d.r0, d.r1, buf, g.y, g.part, d.seg, sh);
+        tile_rows<Y, A, EPI, kBlock, kNTY>(pre, d.r0, d.r1, buf, g.y, g.part, d.seg, sh);
         return;
     }
     // Values narrower than binary64: the runs before the stream, so the
@@ -291,7 +299,7 @@ __global__ __launch_bounds__(kBlock) void k_cwin(SpmvArgs<V, X, Y> g) {
     __syncthreads();
     t.store(pr, buf);
     __syncthreads();
-    tile_rows<Y, A, EPI>(pre, d.r0, d.r1, buf, g.y, g.part, d.seg, sh);
+    tile_rows<Y, A, EPI, kBlock, kNTY>(pre, d.r0, d.r1, buf, g.y, g.part, d.seg, sh);
 }
 
 // Persistent compact windows: the workgroups of an XCD walk its tile range

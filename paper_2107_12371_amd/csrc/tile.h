@@ -227,7 +227,8 @@ template <typename Y, int EPI, int LANES = kBlock> struct RowPre {
 // order, epilogue, optional per-tile partial (fixed-shape reduction).
 // Row sums for a tile worked by LANES lanes (256: a workgroup, reduced with
 // block_sum; 64: one wavefront, reduced with wave_sum, sh unused).
-template <typename Y, typename A, int EPI, int LANES = kBlock>
+// NTY: the plain product's y is stored non-temporally (k_cwin on binary64).
+template <typename Y, typename A, int EPI, int LANES = kBlock, bool NTY = false>
 __device__ __forceinline__ void tile_rows(const RowPre<Y, EPI, LANES> &pre, int r0, int r1,
                                           const A *__restrict__ prod, Y *__restrict__ y,
                                           double *__restrict__ part, int seg, double *sh) {
@@ -262,7 +263,8 @@ __device__ __forceinline__ void tile_rows(const RowPre<Y, EPI, LANES> &pre, int 
                 y[r] = res;
                 dot += static_cast<double>(res) * static_cast<double>(res);
             } else {
-                y[r] = static_cast<Y>(sum);
+                if constexpr (NTY && EPI == EPI_PLAIN) __builtin_nontemporal_store(static_cast<Y>(sum), y + r);
+                else y[r] = static_cast<Y>(sum);
                 if (EPI == EPI_DOT) dot += static_cast<double>(sum) * static_cast<double>(pre.op[i]);
             }
         }
