@@ -4,11 +4,13 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <exception>
 #include <vector>
 
 #include "device.h"
 #include "internal.h"
 #include "bsr.h"
+#include "jag.h"
 #include "launch.h"
 #include "matrix.h"
 #include "spmm.h"
@@ -100,6 +102,30 @@ struct Uploader {
         return SPMV_OK;
     }
 
+    // Allocates n elements for a kernel to fill, zero-filled from element
+    // `used` on.
+    template <typename T> int reserve(T **dst, size_t n, size_t used) {
+        void *p = nullptr;
+        hipError_t e = hipMalloc(&p, sizeof(T) * n);
+        if (e != hipSuccess) return hip_fail(e, "hipMalloc");
+        A->allocs.push_back(p);
+        A->bytes += (int64_t)(sizeof(T) * n);
+        e = hipMemsetAsync(static_cast<T *>(p) + used, 0, sizeof(T) * (n - used), s);
+        if (e != hipSuccess) return hip_fail(e, "hipMemsetAsync");
+        *dst = static_cast<T *>(p);
+        return SPMV_OK;
+    }
+
+    // Frees the allocations after the first `keep`.
+    void release_from(size_t keep, int64_t bytes) {
+        (void)hipStreamSynchronize(s);
+        while (A->allocs.size() > keep) {
+            (void)hipFree(A->allocs.back());
+            A->allocs.pop_back();
+        }
+        A->bytes = bytes;
+    }
+
     // Releases what was allocated so far (failed creation).
     void release_all() {
         for (void *q : A->allocs) (void)hipFree(q);
@@ -170,6 +196,97 @@ static int apply_typed(const spmv_matrix *A, const V *val, const X *x, Y *y, voi
                                              static_cast<hipStream_t>(stream), long_ws);
     if (e != hipSuccess) return hip_fail(e, "spmv launch");
     return SPMV_OK;
+}
+
+// The jagged tiles' arrays, for the value types in `fp64` and the handle's
+// FP32 / BF16 copies.
+static int upload_jag(Uploader &U, DevMatrix &M, const JagPlan &J, const int32_t *row_ptr,
+                      const std::vector<TileDesc> &long_desc, bool fp64) {
+    std::vector<TileDesc> rest;
+    // the rows in no jagged tile, in row tiles (plan.cpp's rule)
+    const int cap = M.tile_nnz - 3;
+    for (const auto &range : J.rest) {
+        for (int32_t r = range.first; r < range.second;) {
+            if (row_ptr[r + 1] - row_ptr[r] > cap) {  // a long row: a segment of its own
+                ++r;
+                continue;
+            }
+            TileDesc d{};
+            d.r0 = r;
+            while (r < range.second && r - d.r0 < 512 && row_ptr[r + 1] - row_ptr[d.r0] <= cap) ++r;
+            d.r1 = r;
+            d.s = row_ptr[d.r0];
+            d.e = row_ptr[d.r1];
+            d.seg = J.n_tiles + (int32_t)rest.size();
+            rest.push_back(d);
+        }
+    }
+    std::vector<TileDesc> lng = long_desc;
+    for (size_t i = 0; i < lng.size(); ++i) lng[i].seg = J.n_tiles + (int32_t)(rest.size() + i);
+    int rc = U.put(&M.jag_hdr, J.hdr.data(), J.hdr.size(), 0);
+    if (!rc) rc = U.put(&M.jag_slot, J.slot.data(), J.slot.size(), 0);
+    if (!rc) rc = U.put(&M.jag_sect, J.sect.data(), J.sect.size(), 0);
+    if (!rc && !rest.empty()) rc = U.put(&M.jag_rest, rest.data(), rest.size(), 0);
+    if (!rc && !lng.empty()) rc = U.put(&M.jag_long, lng.data(), lng.size(), 0);
+    if (rc) return rc;
+    M.n_jag = J.n_tiles;
+    M.jag_stride = J.stride;
+    M.jag_width = J.width;
+    M.jag_groups = J.groups;
+    M.n_jag_rest = (int32_t)rest.size();
+    // a wavefront reads whole: 64 elements of padding past the last entry
+    const size_t ne = (size_t)J.n_entries, nw = (size_t)J.n_words;
+    rc = U.reserve(&M.jag_pos, nw + kWave, nw);
+    if (!rc) launch_jag_fill_pos(M, M.jag_pos, U.s);
+    if (!rc && fp64) {
+        rc = U.reserve(&M.jag64, ne + kWave, ne);
+        if (!rc) launch_jag_fill_val<double>(M, M.val64, M.jag64, U.s);
+    }
+    if (!rc && M.val32) {
+        rc = U.reserve(&M.jag32, ne + kWave, ne);
+        if (!rc) launch_jag_fill_val<float>(M, M.val32, M.jag32, U.s);
+    }
+    if (!rc && M.val16) {
+        rc = U.reserve(&M.jag16, ne + kWave, ne);
+        if (!rc) launch_jag_fill_val<uint16_t>(M, M.val16, M.jag16, U.s);
+    }
+    if (rc) return rc;
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(U.s);
+    return e == hipSuccess ? SPMV_OK : hip_fail(e, "jagged tile layout");
+}
+
+// Jagged tiles beside the handle's plan, where no parameter asks for another
+// kernel: for products with FP32 or BF16 values, and for binary64 ones of
+// plans without compact windows (k_cwin reads as many bytes and is as fast
+// there: 133 us either way on the 4M-row 27-point mesh, where FP32 takes 77.7
+// against 81.0 and BF16 68.0 against 73.2 us).  Without memory for them the handle keeps
+// its row tiles.
+static void add_jag(Uploader &U, DevMatrix &M, const int32_t *row_ptr, const int32_t *col_idx,
+                    const spmv_params *p, const std::vector<TileDesc> &long_desc) {
+    if (p && (p->tile_nnz || p->tile_rows || p->window_mode != SPMV_WINDOW_AUTO || p->window_gap || p->kernel)) return;
+    const bool fp64 = M.n_cwin == 0;
+    if (M.nnz < kJagMinNnz || !(fp64 || M.val32 || M.val16)) return;
+    JagPlan J;
+    try {
+        if (!build_jag_plan(M.n_rows, M.n_cols, M.nnz, row_ptr, col_idx, M.tile_nnz - 3, J)) return;
+    } catch (const std::exception &) {
+        return;
+    }
+    const size_t keep = U.A->allocs.size();
+    const int64_t bytes = U.A->bytes;
+    if (upload_jag(U, M, J, row_ptr, long_desc, fp64) == SPMV_OK) return;
+    (void)hipGetLastError();
+    U.release_from(keep, bytes);
+    M.n_jag = M.n_jag_rest = 0;
+    M.jag_hdr = M.jag_sect = nullptr;
+    M.jag_slot = nullptr;
+    M.jag_pos = nullptr;
+    M.jag64 = nullptr;
+    M.jag32 = nullptr;
+    M.jag16 = nullptr;
+    M.jag_rest = M.jag_long = nullptr;
+    clear_error();
 }
 
 // SPMV_DEVICE_PTRS: copies n elements of a caller's device array into a
@@ -394,8 +511,8 @@ extern "C" int spmv_create(int32_t n_rows, int32_t n_cols, int64_t nnz, const in
     M.n_stream = (int32_t)P.stream_list.size();
     if (!rc && M.n_stream) rc = upload_descs(P.stream_list, &M.stream_desc);
     M.n_long = (int32_t)P.long_list.size();
+    std::vector<TileDesc> d;  // the long rows
     if (!rc && M.n_long) {
-        std::vector<TileDesc> d;
         for (int32_t sg : P.long_list) d.push_back(desc_of(sg));
         rc = U.put(&M.long_desc, d.data(), d.size(), 0);
         if (!rc) rc = upload_long_pieces(U, M, d);
@@ -418,6 +535,7 @@ extern "C" int spmv_create(int32_t n_rows, int32_t n_cols, int64_t nnz, const in
         if (P.seg_kind[sg] != SEG_LONG)
             A->max_tile_entries = std::max(A->max_tile_entries,
                                            row_ptr[P.seg_bound[sg + 1]] - row_ptr[P.seg_bound[sg]]);
+    if (!rc) add_jag(U, M, row_ptr, col_idx, params, d);
     if (!rc) prepare_launch_queries();
     if (!rc && M.n_blk) {
         hipError_t e2 = prepare_window_kernels();

@@ -50,6 +50,7 @@
 
 #include "device.h"
 #include "internal.h"
+#include "jag.h"
 #include "launch.h"
 #include "matrix.h"
 #include "tile.h"
@@ -978,6 +979,7 @@ template <typename T, typename V> struct CgCore {
     CgState *st;        // device
     CgState *hst;       // pinned host mirror
     int n_wg, chunk, graph_iters;
+    int n_part;  // partials an EPI_DOT / EPI_RESID product leaves (the fused product: M.n_seg)
     hipStream_t s;
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
@@ -993,6 +995,7 @@ template <typename T, typename V> struct CgCore {
         n_wg = std::max(1, std::min(2048, (n + 4 * kBlock - 1) / (4 * kBlock)));
         chunk = (n + n_wg - 1) / n_wg;
         graph_iters = n >= (1 << 20) ? 8 : (n >= (1 << 16) ? 16 : 32);
+        n_part = n_partials<V>(M);
         fused = n_wg <= kFoldBeta && chunk <= 4 * kBlock && M.block == 1 && M.format == SPMV_FORMAT_CSR &&
                 M.n_stream > 0 &&
                 M.n_cwin == 0 && M.n_blk == 0 && M.n_long == 0 && M.n_seg == M.n_stream;
@@ -1055,10 +1058,10 @@ template <typename T, typename V> struct CgCore {
         const int *done = &st->done;
         hipError_t e = launch_spmv<V, T, T, T>(M, val, p, q, EPI_DOT, nullptr, part_seg, done, t, long_ws);
         if (e != hipSuccess) return e;
-        const bool fold_alpha = M.n_seg <= kFoldAlpha;
-        if (!fold_alpha) reduce(part_seg, M.n_seg, R_ALPHA, t);
+        const bool fold_alpha = n_part <= kFoldAlpha;
+        if (!fold_alpha) reduce(part_seg, n_part, R_ALPHA, t);
         hipLaunchKernelGGL((k_update_xr<T>), dim3(n_wg), dim3(kBlock), 0, t, n, chunk, x, r, p, q, st, part_seg,
-                           fold_alpha ? M.n_seg : -1, part_vec);
+                           fold_alpha ? n_part : -1, part_vec);
         if (n_wg <= kFoldBeta) {
             hipLaunchKernelGGL((k_update_p_fold<T>), dim3(grid_for(n)), dim3(kBlock), 0, t, n, p, r, st, part_vec,
                                n_wg);
@@ -1110,7 +1113,7 @@ template <typename T, typename V> struct CgCore {
     hipError_t true_residual(const T *b) {
         hipError_t e = launch_spmv<V, T, T, T>(M, val, x, r, EPI_RESID, b, part_seg, nullptr, s, long_ws);
         if (e != hipSuccess) return e;
-        reduce(part_seg, M.n_seg, R_TRUE, s);
+        reduce(part_seg, n_part, R_TRUE, s);
         return hipGetLastError();
     }
 
@@ -1121,7 +1124,7 @@ template <typename T, typename V> struct CgCore {
     int solve(const T *b, double tol, int max_iter, int *iters, int *replacements, bool confirm = true) {
         hipLaunchKernelGGL(k_init_state, dim3(1), dim3(1), 0, s, st, tol, max_iter);
         HIP_TRY(true_residual(b));
-        reduce(part_seg, M.n_seg, R_RHO0, s);
+        reduce(part_seg, n_part, R_RHO0, s);
         if (fused) {
             // p = 0 and beta = 0: the first fused product gathers p_new = r
             hipLaunchKernelGGL((k_zero<T>), dim3(grid_for(n)), dim3(kBlock), 0, s, n, p);
@@ -1188,7 +1191,7 @@ int alloc_core(Buffers &B, CgCore<T, V> &C) {
     HIP_TRY(B.alloc(&C.r, C.n));
     HIP_TRY(B.alloc(&C.p, C.n));
     HIP_TRY(B.alloc(&C.q, C.n));
-    HIP_TRY(B.alloc(&C.part_seg, (size_t)std::max(C.M.n_seg, 1)));
+    HIP_TRY(B.alloc(&C.part_seg, (size_t)std::max({C.M.n_seg, C.n_part, 1})));
     HIP_TRY(B.alloc(&C.part_vec, (size_t)C.n_wg));
     HIP_TRY(B.alloc(&C.part2, (size_t)CgCore<T, V>::kStage1));
     if (C.M.piece_long) HIP_TRY(B.alloc(&C.long_ws, (size_t)C.M.n_long_pieces));
@@ -1219,10 +1222,10 @@ struct PcgCore : CgCore<double, double> {
                                                                      long_ws);
         if (e != hipSuccess) return e;
         if (jacobi) {
-            const bool fold_alpha = M.n_seg <= kFoldAlpha;
-            if (!fold_alpha) reduce(part_seg, M.n_seg, R_ALPHA, ts);
+            const bool fold_alpha = n_part <= kFoldAlpha;
+            if (!fold_alpha) reduce(part_seg, n_part, R_ALPHA, ts);
             hipLaunchKernelGGL(k_update_xr_jacobi, dim3(n_wg), dim3(kBlock), 0, ts, n, chunk, x, r, p, q, dinv, z,
-                               st, part_seg, fold_alpha ? M.n_seg : -1, part_vec, part_rz);
+                               st, part_seg, fold_alpha ? n_part : -1, part_vec, part_rz);
             if (n_wg <= kFoldBeta) {
                 hipLaunchKernelGGL(k_update_p_pcg, dim3(grid_for(n)), dim3(kBlock), 0, ts, n, p, z, st, part_vec,
                                    part_rz, n_wg);
@@ -1232,10 +1235,10 @@ struct PcgCore : CgCore<double, double> {
             }
             return hipGetLastError();
         }
-        const bool fold_alpha = M.n_seg <= kFoldAlpha, fold_beta = n_wg <= kFoldBeta;
-        if (!fold_alpha) reduce(part_seg, M.n_seg, R_ALPHA, ts);
+        const bool fold_alpha = n_part <= kFoldAlpha, fold_beta = n_wg <= kFoldBeta;
+        if (!fold_alpha) reduce(part_seg, n_part, R_ALPHA, ts);
         hipLaunchKernelGGL(k_update_xr_pcg, dim3(n_wg), dim3(kBlock), 0, ts, n, chunk, x, r, p, q, dinv, t, st,
-                           part_seg, fold_alpha ? M.n_seg : -1, part_vec);
+                           part_seg, fold_alpha ? n_part : -1, part_vec);
         // folded: the convergence test waits for the p update, so on the last
         // iteration the preconditioner runs once more (it writes neither x nor r)
         if (!fold_beta) reduce(part_vec, n_wg, R_RR, ts);
@@ -1397,7 +1400,7 @@ struct Cg1Core : CgCore<double, double> {
         if (e != hipSuccess) return e;
         e = launch_spmv<double, double, double, double>(M, val, r, w[0], EPI_DOT, nullptr, part_seg, nullptr, s);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_cg1_start, dim3(1), dim3(kBlock), 0, s, st, sc + 1, part_seg, M.n_seg);
+        hipLaunchKernelGGL(k_cg1_start, dim3(1), dim3(kBlock), 0, s, st, sc + 1, part_seg, n_part);
         hipLaunchKernelGGL((k_zero<double>), dim3(grid_for(n)), dim3(kBlock), 0, s, n, p);
         hipLaunchKernelGGL((k_zero<double>), dim3(grid_for(n)), dim3(kBlock), 0, s, n, sv[0]);
         return hipGetLastError();

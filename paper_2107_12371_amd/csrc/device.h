@@ -5,6 +5,8 @@
 
 #include <cstdint>
 
+#include "jag_limits.h"
+
 namespace spmvlib {
 
 constexpr int kBlock = 256;        // threads per workgroup (4 wavefronts of 64)
@@ -66,6 +68,19 @@ struct DevMatrix {
     int32_t *runs = nullptr;         // (first column, window position) per run
     uint16_t *lidx = nullptr;        // window-relative column per stored entry (+ padding)
     uint32_t *lidx12 = nullptr;      // 2048-entry tiles: packed 12-bit positions per tile and lane
+    // jagged window tiles (jag.hip), for the value types that have a copy of
+    // the values in that order
+    int32_t n_jag = 0, jag_stride = 0, jag_width = 0, jag_groups = 0;
+    int32_t *jag_hdr = nullptr;      // kJagHdr per slice
+    uint16_t *jag_slot = nullptr;    // kJagRows per tile
+    int32_t *jag_sect = nullptr;     // jag_stride per tile
+    uint32_t *jag_pos = nullptr;     // packed 12-bit positions (+ a wavefront of padding)
+    double *jag64 = nullptr;         // values (+ a wavefront of padding)
+    float *jag32 = nullptr;
+    uint16_t *jag16 = nullptr;
+    int32_t n_jag_rest = 0;
+    TileDesc *jag_rest = nullptr;    // direct-gather tiles of the rows in no jagged tile
+    TileDesc *jag_long = nullptr;    // long_desc with the jagged product's partial numbers
     bool xcd_remap = true;
     int32_t xcd_chunk_log2 = -1;     // XCD assignment (xcd_tile): -1 one contiguous range per XCD
     int32_t kernel = KV_AUTO;        // direct-gather kernel variant

@@ -4,8 +4,10 @@
 #include <cstdint>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
+#include "jag_limits.h"
 #include "spmv.h"
 
 namespace spmvlib {
@@ -92,6 +94,39 @@ struct Plan {
 
 constexpr int kPackTileNnz = 2048;  // tile capacity with packed 12-bit positions
 constexpr int kPackLanes = 256;     // lanes per workgroup; each lane owns 4 entries per 1024-entry pass
+
+// Jagged window tiles (jag.hip): up to kJagRows consecutive rows of at most
+// kJagMaxLen entries each, sorted by length and cut into slices of one
+// wavefront; windows of at most kJagMaxSectors sectors of kJagSector words,
+// so that 12 bits hold a position. 
+constexpr int kJagSlice = 64;
+// Matrices with fewer stored entries keep the row tiles alone: one launch
+// takes 2.4-3.2 us there and the row tiles' workgroups, being smaller, fill
+// the GPU sooner (50K-440K entries: 2.4-2.9 us against 2.7-3.7 us), while from
+// 1M entries on the jagged tiles are faster in every mesh and precision
+// (1.2M-entry tet mesh FP64 / FP32 4.0 / 4.0 -> 3.7 / 2.9 us, 3.5M-entry kNN
+// 11.0 / 8.2 -> 8.7 / 4.3, 16.7M-entry 27-point 33.9 / 30.1 -> 28.5 / 17.6).
+constexpr int64_t kJagMinNnz = int64_t(1) << 20;
+
+struct JagPlan {
+    int32_t n_tiles = 0;
+    int32_t stride = 0;             // sectors held per tile
+    int32_t width = 0;              // window words of the widest tile
+    int32_t groups = 0;             // groups of 4 entries of the longest row
+    int64_t n_entries = 0;          // values
+    int64_t n_words = 0;            // position words
+    std::vector<int32_t> hdr;       // kJagHdr per slice: first value, first position word, sectors,
+                                    // first row, rows, sector past x's end, 0, 0, 32 run lengths (bytes)
+    std::vector<uint16_t> slot;     // per tile and lane: row length << 8 | row in the tile
+    std::vector<int32_t> sect;      // stride per tile, ascending
+    std::vector<std::pair<int32_t, int32_t>> rest;  // row ranges in no tile
+};
+
+// The layout, or false where row tiles serve the matrix better (scattered
+// columns, long rows).  Rows longer than long_len are not counted: they take
+// the long-row path either way.
+bool build_jag_plan(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *row_ptr, const int32_t *col_idx,
+                    int long_len, JagPlan &J);
 
 // Sliced ELLPACK with sigma sorting (SELL-C-sigma; the paper's sliced
 // ELLPACK storage, Sec. 4.2, with C = 64 rows per slice, one per lane of a

@@ -1,0 +1,170 @@
+// Host-side layout of the jagged window tiles: which rows form tiles, each
+// tile's lanes in order of row length, its window's sectors, and its slices'
+// headers.  Pure C++ (no HIP calls); the positions and values are then
+// filled on the device from the CSR arrays.
+#include <algorithm>
+#include <atomic>
+#include <cstring>
+#include <new>
+#include <system_error>
+#include <thread>
+
+#include "internal.h"
+
+namespace spmvlib {
+
+// Runs work(t) for t < n on up to n threads; a thread that cannot be started
+// has its share run here.
+template <typename F> static void run_shares(int n, F &&work) {
+    std::vector<std::thread> th;
+    int t = 1;
+    try {
+        th.reserve((size_t)n);
+        for (; t < n; ++t) th.emplace_back(work, t);
+    } catch (const std::exception &) {
+    }
+    work(0);
+    for (; t < n; ++t) work(t);
+    for (auto &x : th) x.join();
+}
+
+bool build_jag_plan(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *row_ptr, const int32_t *col_idx,
+                    int long_len, JagPlan &J) {
+    J = JagPlan{};
+    const auto len_of = [row_ptr](int32_t r) { return row_ptr[r + 1] - row_ptr[r]; };
+    // runs of rows of at most kJagMaxLen entries, in tiles of 256 rows
+    std::vector<int32_t> first, rows;
+    int64_t long_entries = 0;
+    for (int32_t r = 0; r < n_rows;) {
+        if (len_of(r) > kJagMaxLen) {
+            if (len_of(r) > long_len) long_entries += len_of(r);
+            ++r;
+            continue;
+        }
+        int32_t r1 = r + 1;
+        while (r1 < n_rows && r1 - r < kJagRows && len_of(r1) <= kJagMaxLen) ++r1;
+        first.push_back(r);
+        rows.push_back(r1 - r);
+        r = r1;
+    }
+    const int32_t n_cand = (int32_t)first.size();
+    // tiles cut short by longer rows leave lanes idle
+    if (n_cand == 0 || (int64_t)n_cand * (kJagRows / 2) > n_rows) return false;
+    const int nth = std::max(1, std::min({32, (int)std::thread::hardware_concurrency(), n_cand / 64}));
+    std::vector<std::vector<int32_t>> lists(nth);
+    std::vector<int64_t> off((size_t)n_cand, 0);
+    std::vector<int32_t> count((size_t)n_cand, -1);  // sectors; -1: the window does not fit
+    std::atomic<bool> failed{false};
+    run_shares(nth, [&](int t) {
+        try {
+            std::vector<int32_t> seen((size_t)n_cols / kJagSector + 1, -1);
+            std::vector<int32_t> u;
+            std::vector<int32_t> &out = lists[t];
+            // contiguous shares: the tiles' lists follow each other in order
+            const int32_t c0 = (int32_t)((int64_t)n_cand * t / nth), c1 = (int32_t)((int64_t)n_cand * (t + 1) / nth);
+            for (int32_t i = c0; i < c1; ++i) {
+                u.clear();
+                const int32_t s = row_ptr[first[i]], e = row_ptr[first[i] + rows[i]];
+                for (int32_t k = s; k < e && (int)u.size() <= kJagMaxSectors; ++k) {
+                    const int32_t sc = col_idx[k] / kJagSector;
+                    if (seen[sc] != i) {
+                        seen[sc] = i;
+                        u.push_back(sc);
+                    }
+                }
+                if ((int)u.size() > kJagMaxSectors) continue;
+                std::sort(u.begin(), u.end());
+                off[i] = (int64_t)out.size();
+                count[i] = (int32_t)u.size();
+                out.insert(out.end(), u.begin(), u.end());
+            }
+        } catch (const std::exception &) {
+            failed = true;
+        }
+    });
+    if (failed) return false;
+    // Worth it when nearly all of the entries that row tiles would work lie
+    // in the tiles and the staged words do not outnumber them (a scattered
+    // ordering touches a sector of 8 words per entry, and gathering x
+    // directly reads less).
+    int64_t entries = 0, words = 0;
+    int32_t most = 0;
+    for (int32_t i = 0; i < n_cand; ++i) {
+        if (count[i] < 0) continue;
+        entries += row_ptr[first[i] + rows[i]] - row_ptr[first[i]];
+        words += (int64_t)count[i] * kJagSector;
+        most = std::max(most, count[i]);
+        ++J.n_tiles;
+    }
+    if (J.n_tiles == 0 || 8 * entries < 7 * (nnz - long_entries) || words > entries) return false;
+    J.stride = std::max((most + 15) / 16 * 16, 16);
+    J.width = most * kJagSector;
+    constexpr int kSlices = kJagRows / kJagSlice;
+    const size_t nt = (size_t)J.n_tiles;
+    if (nt * J.stride > (size_t)INT32_MAX) return false;
+    J.hdr.assign(nt * kSlices * kJagHdr, 0);
+    J.slot.resize(nt * kJagRows);
+    J.sect.assign(nt * J.stride, 0);
+    int64_t vb = 0, pb = 0;
+    int32_t t = 0, longest = 0;
+    std::vector<int32_t> tile_of((size_t)n_cand, -1);
+    for (int32_t i = 0; i < n_cand; ++i)
+        if (count[i] >= 0) tile_of[i] = t++;
+    // lanes in order of row length (longest first), counts of the slices' runs
+    run_shares(nth, [&](int sh) {
+        const int32_t c0 = (int32_t)((int64_t)n_cand * sh / nth), c1 = (int32_t)((int64_t)n_cand * (sh + 1) / nth);
+        for (int32_t i = c0; i < c1; ++i) {
+            if (tile_of[i] < 0) continue;
+            const size_t tile = (size_t)tile_of[i];
+            std::memcpy(&J.sect[tile * J.stride], lists[sh].data() + off[i], sizeof(int32_t) * (size_t)count[i]);
+            uint16_t *slot = &J.slot[tile * kJagRows];
+            int at[kJagMaxLen + 1] = {};
+            for (int32_t r = 0; r < kJagRows; ++r) ++at[r < rows[i] ? len_of(first[i] + r) : 0];
+            for (int l = kJagMaxLen, sum = 0; l >= 0; --l) {
+                const int n = at[l];
+                at[l] = sum;
+                sum += n;
+            }
+            for (int32_t r = 0; r < kJagRows; ++r) {
+                const int l = r < rows[i] ? len_of(first[i] + r) : 0;
+                slot[at[l]++] = (uint16_t)(l << 8 | r);
+            }
+            for (int sl = 0; sl < kSlices; ++sl) {
+                int32_t *h = &J.hdr[(tile * kSlices + sl) * kJagHdr];
+                h[2] = count[i];
+                h[3] = first[i];
+                h[4] = rows[i];
+                // a sector reaching past x's last word needs word-wise staging
+                h[5] = count[i] > 0 && ((int64_t)J.sect[tile * J.stride + count[i] - 1] + 1) * kJagSector > n_cols;
+                uint8_t *c = reinterpret_cast<uint8_t *>(h + 8);
+                for (int l = 0; l < kJagSlice; ++l)
+                    for (int j = 0; j < slot[sl * kJagSlice + l] >> 8; ++j) ++c[j];
+            }
+        }
+    });
+    for (size_t sl = 0; sl < nt * kSlices; ++sl) {
+        int32_t *h = &J.hdr[sl * kJagHdr];
+        const uint8_t *c = reinterpret_cast<const uint8_t *>(h + 8);
+        h[0] = (int32_t)vb;
+        h[1] = (int32_t)pb;
+        for (int j = 0; j < kJagMaxLen; ++j) {
+            vb += c[j];
+            if (j % 8 == 0 || j % 8 == 2 || j % 8 == 5) pb += c[j];
+            if (c[j]) longest = std::max(longest, j + 1);
+        }
+    }
+    J.n_entries = vb;
+    J.n_words = pb;
+    J.groups = (longest + 3) / 4;
+    // the rows left to row tiles (long rows are segments of their own)
+    int32_t r = 0;
+    for (int32_t i = 0; i <= n_cand; ++i) {
+        if (i < n_cand && count[i] < 0) continue;
+        const int32_t stop = i < n_cand ? first[i] : n_rows;
+        if (stop > r) J.rest.emplace_back(r, stop);
+        if (i < n_cand) r = first[i] + rows[i];
+    }
+    return true;
+}
+
+}  // namespace spmvlib

@@ -37,6 +37,7 @@
 #include <hip/hip_runtime.h>
 
 #include "device.h"
+#include "jag.h"
 #include "launch.h"
 #include "sell.h"
 #include "spmv.h"
@@ -559,10 +560,10 @@ template <typename Y> static double *y_scratch(const DevMatrix &M, Y *y) {
 // workgroup per row.  Both give the same bits.  Launched before the row
 // tiles (the output's scratch rows are theirs to write afterwards).
 template <typename V, typename X, typename Y, typename A, int EPI>
-static void launch_long(const DevMatrix &M, SpmvArgs<V, X, Y> g, hipStream_t st) {
+static void launch_long(const DevMatrix &M, SpmvArgs<V, X, Y> g, const TileDesc *desc, hipStream_t st) {
     if (M.n_long <= 0) return;
     SpmvArgs<V, X, Y> a = g;
-    a.desc = M.long_desc;
+    a.desc = desc;
     a.n_list = M.n_long;
     double *ws = nullptr;
     if (M.piece_long && M.long_split) ws = g.long_ws ? g.long_ws : y_scratch(M, g.y);
@@ -577,9 +578,28 @@ static void launch_long(const DevMatrix &M, SpmvArgs<V, X, Y> g, hipStream_t st)
     }
 }
 
+// One workgroup per direct-gather tile of `desc`.
+template <typename V, typename X, typename Y, typename A, int NT, int EPI>
+static void launch_stream(const DevMatrix &M, SpmvArgs<V, X, Y> a, const TileDesc *desc, int n, hipStream_t st) {
+    a.desc = desc;
+    a.n_list = n;
+    a.per_xcd = M.xcd_remap && n >= 16 ? (n + 7) / 8 : 0;
+    a.chunk_log2 = M.xcd_chunk_log2;
+    const int grid = xcd_grid(n, a.per_xcd, a.chunk_log2);
+    hipLaunchKernelGGL((k_stream<V, X, Y, A, NT, EPI>), dim3(grid), dim3(kBlock), 0, st, a);
+}
+
 template <typename V, typename X, typename Y, typename A, int NT, int EPI>
 static hipError_t launch_nt(const DevMatrix &M, SpmvArgs<V, X, Y> g, hipStream_t st) {
-    launch_long<V, X, Y, A, EPI>(M, g, st);
+    if (const V *jv = jag_values<V>(M)) {
+        // jagged tiles where the handle has them for this value type, and
+        // row tiles for the few rows they leave out
+        launch_long<V, X, Y, A, EPI>(M, g, M.jag_long, st);
+        launch_jag<V, X>(M, jv, g, EPI, st);
+        if (M.n_jag_rest > 0) launch_stream<V, X, Y, A, NT, EPI>(M, g, M.jag_rest, M.n_jag_rest, st);
+        return hipGetLastError();
+    }
+    launch_long<V, X, Y, A, EPI>(M, g, M.long_desc, st);
     if (M.n_stream > 0) {
         SpmvArgs<V, X, Y> a = g;
         a.desc = M.stream_desc;
@@ -600,11 +620,7 @@ static hipError_t launch_nt(const DevMatrix &M, SpmvArgs<V, X, Y> g, hipStream_t
             a.wg_per_xcd = std::max(1, std::min(a.per_xcd, resident));
             hipLaunchKernelGGL((k_pipe<V, X, Y, A, NT, EPI>), dim3(8 * a.wg_per_xcd), dim3(kBlock), 0, st, a);
         } else {
-            a.per_xcd = 0;
-            a.chunk_log2 = M.xcd_chunk_log2;
-            if (M.xcd_remap && M.n_stream >= 16) a.per_xcd = (M.n_stream + 7) / 8;
-            const int grid = xcd_grid(M.n_stream, a.per_xcd, a.chunk_log2);
-            hipLaunchKernelGGL((k_stream<V, X, Y, A, NT, EPI>), dim3(grid), dim3(kBlock), 0, st, a);
+            launch_stream<V, X, Y, A, NT, EPI>(M, g, M.stream_desc, M.n_stream, st);
         }
     }
     if (M.n_cwin > 0) {
@@ -644,7 +660,7 @@ static hipError_t launch_nt(const DevMatrix &M, SpmvArgs<V, X, Y> g, hipStream_t
 
 template <typename V, typename X, typename Y, typename A, int EPI>
 static hipError_t launch_sell(const DevMatrix &M, SpmvArgs<V, X, Y> g, hipStream_t st) {
-    launch_long<V, X, Y, A, EPI>(M, g, st);
+    launch_long<V, X, Y, A, EPI>(M, g, M.long_desc, st);
     if (M.n_sell_wg > 0) launch_sell_slices<V, X, Y, A>(M, g, EPI, st);
     return hipGetLastError();
 }
