@@ -14,6 +14,7 @@
 #include "launch.h"
 #include "matrix.h"
 #include "spmm.h"
+#include "sweep.h"
 
 namespace spmvlib {
 
@@ -100,6 +101,26 @@ struct Uploader {
         if (e != hipSuccess) return hip_fail(e, "upload");
         *dst = static_cast<T *>(p);
         return SPMV_OK;
+    }
+
+    // put for a source in host memory or, with on_device, in device (or
+    // managed) memory.
+    template <typename T> int put_from(T **dst, const T *src, bool on_device, size_t n, size_t alloc_n) {
+        if (!on_device) return put(dst, src, n, alloc_n);
+        int rc = reserve(dst, alloc_n, n);
+        if (rc || !n) return rc;
+        hipError_t e = hipMemcpyAsync(*dst, src, sizeof(T) * n, hipMemcpyDefault, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        return e == hipSuccess ? SPMV_OK : hip_fail(e, "copy of the values");
+    }
+
+    // A rounded copy of `src` (resident doubles), zero-filled from element n on.
+    template <typename T> int put_rounded(T **dst, const double *src, size_t n, size_t alloc_n) {
+        int rc = reserve(dst, alloc_n, n);
+        if (rc) return rc;
+        hipError_t e = launch_round_values(src, *dst, (int64_t)n, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        return e == hipSuccess ? SPMV_OK : hip_fail(e, "rounding of the values");
     }
 
     // Allocates n elements for a kernel to fill, zero-filled from element
@@ -256,45 +277,81 @@ static int upload_jag(Uploader &U, DevMatrix &M, const JagPlan &J, const int32_t
     return e == hipSuccess ? SPMV_OK : hip_fail(e, "jagged tile layout");
 }
 
-// Jagged tiles beside the handle's plan, where no parameter asks for another
-// kernel: for products with FP32 or BF16 values, and for binary64 ones of
-// plans without compact windows (k_cwin reads as many bytes and is as fast
-// there: 133 us either way on the 4M-row 27-point mesh, where FP32 takes 77.7
-// against 81.0 and BF16 68.0 against 73.2 us).  Without memory for them the handle keeps
-// its row tiles.
-static void add_jag(Uploader &U, DevMatrix &M, const int32_t *row_ptr, const int32_t *col_idx,
-                    const spmv_params *p, const std::vector<TileDesc> &long_desc) {
-    if (p && (p->tile_nnz || p->tile_rows || p->window_mode != SPMV_WINDOW_AUTO || p->window_gap || p->kernel)) return;
-    const bool fp64 = M.n_cwin == 0;
-    if (M.nnz < kJagMinNnz || !(fp64 || M.val32 || M.val16)) return;
-    JagPlan J;
-    try {
-        if (!build_jag_plan(M.n_rows, M.n_cols, M.nnz, row_ptr, col_idx, M.tile_nnz - 3, J)) return;
-    } catch (const std::exception &) {
-        return;
+// The sweep tiles' arrays.
+static int upload_sweep(Uploader &U, DevMatrix &M, const SweepPlan &S, const int32_t *row_ptr) {
+    std::vector<TileDesc> d(S.bound.size() / 2);
+    for (size_t i = 0; i < d.size(); ++i) {
+        d[i] = TileDesc{};
+        d[i].r0 = S.bound[2 * i];
+        d[i].r1 = S.bound[2 * i + 1];
+        d[i].s = row_ptr[d[i].r0];
+        d[i].e = row_ptr[d[i].r1];
     }
+    const size_t n = S.n, n_pad = n + kPad;
+    int rc = U.put(&M.sweep_desc, d.data(), d.size(), 0);
+    if (!rc) rc = U.put(&M.sweep_place, S.place.get(), n, n_pad);
+    if (rc) return rc;
+    M.n_sweep = (int32_t)d.size();
+    M.sweep_width = S.width;
+    rc = U.reserve(&M.sweep_col, n_pad, n);
+    if (!rc) launch_sweep_fill(M, M.sweep_col, U.s);
+    if (!rc) {
+        rc = U.reserve(&M.sweep64, n_pad, n);
+        if (!rc) launch_sweep_fill_val<double>(M, M.val64, M.sweep64, U.s);
+    }
+    if (!rc && M.val32) {
+        rc = U.reserve(&M.sweep32, n_pad, n);
+        if (!rc) launch_sweep_fill_val<float>(M, M.val32, M.sweep32, U.s);
+    }
+    if (!rc && M.val16 && sweep_pays<float>(M)) {
+        rc = U.reserve(&M.sweep16, n_pad, n);
+        if (!rc) launch_sweep_fill_val<uint16_t>(M, M.val16, M.sweep16, U.s);
+    }
+    if (rc) return rc;
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipStreamSynchronize(U.s);
+    if (e == hipSuccess) e = prepare_sweep_kernels();
+    return e == hipSuccess ? SPMV_OK : hip_fail(e, "sweep tile layout");
+}
+
+// A further layout beside the handle's plan, where no parameter asks for
+// another kernel: jagged tiles for products with FP32 or BF16 values and for
+// binary64 ones of plans without compact windows (k_cwin reads as many bytes
+// and is as fast there: 133 us either way on the 4M-row 27-point mesh, where
+// FP32 takes 77.7 against 81.0 and BF16 68.0 against 73.2 us); sweep tiles for
+// plans without windows whose columns are scattered.  Without memory for a
+// layout the handle keeps its row tiles.
+static void add_layouts(Uploader &U, DevMatrix &M, const int32_t *row_ptr, const int32_t *col_idx,
+                        const spmv_params *p, const std::vector<TileDesc> &long_desc) {
+    if (p && (p->tile_nnz || p->tile_rows || p->window_mode != SPMV_WINDOW_AUTO || p->window_gap || p->kernel)) return;
+    const bool plain = M.n_cwin == 0;
+    if (M.nnz < kJagMinNnz || !(plain || M.val32 || M.val16)) return;
+    const DevMatrix before = M;
     const size_t keep = U.A->allocs.size();
     const int64_t bytes = U.A->bytes;
-    if (upload_jag(U, M, J, row_ptr, long_desc, fp64) == SPMV_OK) return;
+    int rc = SPMV_OK;
+    try {
+        JagPlan J;
+        SweepPlan S;
+        const int cap = M.tile_nnz - 3;
+        if (build_jag_plan(M.n_rows, M.n_cols, M.nnz, row_ptr, col_idx, cap, J))
+            rc = upload_jag(U, M, J, row_ptr, long_desc, plain);
+        else if (plain && sweep_pays<double>(M) &&
+                 build_sweep_plan(M.n_rows, M.n_cols, row_ptr, col_idx, cap, device_cus(), S))
+            rc = upload_sweep(U, M, S, row_ptr);
+    } catch (const std::exception &) {
+        rc = SPMV_ENOMEM;
+    }
+    if (rc == SPMV_OK) return;
     (void)hipGetLastError();
     U.release_from(keep, bytes);
-    M.n_jag = M.n_jag_rest = 0;
-    M.jag_hdr = M.jag_sect = nullptr;
-    M.jag_slot = nullptr;
-    M.jag_pos = nullptr;
-    M.jag64 = nullptr;
-    M.jag32 = nullptr;
-    M.jag16 = nullptr;
-    M.jag_rest = M.jag_long = nullptr;
+    M = before;
     clear_error();
 }
 
-// SPMV_DEVICE_PTRS: copies n elements of a caller's device array into a
-// host vector (the plan is built on the host).  A pointer that the runtime
-// does not know as device or managed memory is SPMV_EINVAL.
-template <typename T> static int fetch_device(const T *src, size_t n, std::vector<T> &dst, const char *what) {
-    dst.resize(n);
-    if (n == 0) return SPMV_OK;
+// SPMV_DEVICE_PTRS: a pointer that the runtime does not know as device or
+// managed memory is SPMV_EINVAL.
+static int check_device(const void *src, const char *what) {
     if (!src) return fail(SPMV_EINVAL, "%s is NULL", what);
     hipPointerAttribute_t attr{};
     if (hipPointerGetAttributes(&attr, src) != hipSuccess ||
@@ -302,6 +359,16 @@ template <typename T> static int fetch_device(const T *src, size_t n, std::vecto
         (void)hipGetLastError();
         return fail(SPMV_EINVAL, "%s is not device memory (SPMV_DEVICE_PTRS)", what);
     }
+    return SPMV_OK;
+}
+
+// Copies n elements of a caller's device array into a host vector (the plan
+// is built on the host).
+template <typename T> static int fetch_device(const T *src, size_t n, std::vector<T> &dst, const char *what) {
+    dst.resize(n);
+    if (n == 0) return SPMV_OK;
+    const int rc = check_device(src, what);
+    if (rc) return rc;
     std::lock_guard<std::mutex> lock(capture_gate());
     hipStream_t s = nullptr;
     hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
@@ -421,34 +488,14 @@ static int create_sell(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_
 
 using namespace spmvlib;
 
-extern "C" int spmv_create(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *row_ptr,
-                           const int32_t *col_idx, const double *values, uint32_t flags,
-                           const spmv_params *params, spmv_matrix **out) {
-    clear_error();
-    if (!out) return fail(SPMV_EINVAL, "out is NULL");
-    *out = nullptr;
-    if (flags & ~(SPMV_VALUES_FP32 | SPMV_VALUES_BF16 | SPMV_NO_XCD_REMAP | SPMV_DEVICE_PTRS))
-        return fail(SPMV_EINVAL, "unknown flags 0x%x", flags);
-    if (flags & SPMV_DEVICE_PTRS) {
-        if (n_rows < 0 || nnz < 0) return fail(SPMV_EINVAL, "n_rows = %d, nnz = %lld", n_rows, (long long)nnz);
-        std::vector<int32_t> rp, ci;
-        std::vector<double> va;
-        int rc = fetch_device(row_ptr, (size_t)n_rows + 1, rp, "row_ptr");
-        if (!rc) rc = fetch_device(col_idx, (size_t)nnz, ci, "col_idx");
-        if (!rc) rc = fetch_device(values, (size_t)nnz, va, "values");
-        if (rc) return rc;
-        return spmv_create(n_rows, n_cols, nnz, rp.data(), nnz ? ci.data() : nullptr, nnz ? va.data() : nullptr,
-                           flags & ~SPMV_DEVICE_PTRS, params, out);
-    }
-    int rc = validate_csr(n_rows, n_cols, nnz, row_ptr, col_idx);
-    if (rc) return rc;
-    if (nnz > 0 && !values) return fail(SPMV_EINVAL, "values is NULL with nnz > 0");
-    if (params && params->format != SPMV_FORMAT_CSR) {
-        if (params->format != SPMV_FORMAT_SELL) return fail(SPMV_EINVAL, "format = %d unknown", params->format);
-        return create_sell(n_rows, n_cols, nnz, row_ptr, col_idx, values, flags, *params, out);
-    }
+// A CSR-format handle from a validated host pattern; the values lie in host
+// memory or, with dev_values, in device memory (they are copied there, never
+// to the host).
+static int create_csr(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *row_ptr, const int32_t *col_idx,
+                      const double *values, bool dev_values, uint32_t flags, const spmv_params *params,
+                      spmv_matrix **out) {
     Plan P;
-    rc = build_plan(n_rows, n_cols, nnz, row_ptr, col_idx, params, P);
+    int rc = build_plan(n_rows, n_cols, nnz, row_ptr, col_idx, params, P);
     if (rc) return rc;
 
     auto *A = new (std::nothrow) spmv_matrix();
@@ -477,17 +524,9 @@ extern "C" int spmv_create(int32_t n_rows, int32_t n_cols, int64_t nnz, const in
     const size_t nz = (size_t)nnz, nz_pad = ((nz + 3) & ~(size_t)3) + kPad;
     rc = U.put(&M.row_ptr, row_ptr, (size_t)n_rows + 1, (size_t)n_rows + 1);
     if (!rc) rc = U.put(&M.col, col_idx, nz, nz_pad);
-    if (!rc) rc = U.put(&M.val64, values, nz, nz_pad);
-    if (!rc && (flags & SPMV_VALUES_FP32)) {
-        std::vector<float> v32(nz);
-        for (size_t k = 0; k < nz; ++k) v32[k] = (float)values[k];
-        rc = U.put(&M.val32, v32.data(), nz, nz_pad);
-    }
-    if (!rc && (flags & SPMV_VALUES_BF16)) {
-        std::vector<uint16_t> v16(nz);
-        for (size_t k = 0; k < nz; ++k) v16[k] = to_bf16((float)values[k]);
-        rc = U.put(&M.val16, v16.data(), nz, nz_pad);
-    }
+    if (!rc) rc = U.put_from(&M.val64, values, dev_values, nz, nz_pad);
+    if (!rc && (flags & SPMV_VALUES_FP32)) rc = U.put_rounded(&M.val32, M.val64, nz, nz_pad);
+    if (!rc && (flags & SPMV_VALUES_BF16)) rc = U.put_rounded(&M.val16, M.val64, nz, nz_pad);
     M.n_seg = P.n_seg();
     M.kernel = P.kernel;
     auto desc_of = [&](int32_t sg) {
@@ -535,7 +574,7 @@ extern "C" int spmv_create(int32_t n_rows, int32_t n_cols, int64_t nnz, const in
         if (P.seg_kind[sg] != SEG_LONG)
             A->max_tile_entries = std::max(A->max_tile_entries,
                                            row_ptr[P.seg_bound[sg + 1]] - row_ptr[P.seg_bound[sg]]);
-    if (!rc) add_jag(U, M, row_ptr, col_idx, params, d);
+    if (!rc) add_layouts(U, M, row_ptr, col_idx, params, d);
     if (!rc) prepare_launch_queries();
     if (!rc && M.n_blk) {
         hipError_t e2 = prepare_window_kernels();
@@ -571,6 +610,43 @@ extern "C" int spmv_create(int32_t n_rows, int32_t n_cols, int64_t nnz, const in
     I.y_scratch_ok = M.piece_long && M.long_split && (int64_t)M.y_ws_rows >= M.n_long_pieces;
     *out = A;
     return SPMV_OK;
+}
+
+extern "C" int spmv_create(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *row_ptr,
+                           const int32_t *col_idx, const double *values, uint32_t flags,
+                           const spmv_params *params, spmv_matrix **out) {
+    clear_error();
+    if (!out) return fail(SPMV_EINVAL, "out is NULL");
+    *out = nullptr;
+    if (flags & ~(SPMV_VALUES_FP32 | SPMV_VALUES_BF16 | SPMV_NO_XCD_REMAP | SPMV_DEVICE_PTRS))
+        return fail(SPMV_EINVAL, "unknown flags 0x%x", flags);
+    if (flags & SPMV_DEVICE_PTRS) {
+        if (n_rows < 0 || nnz < 0) return fail(SPMV_EINVAL, "n_rows = %d, nnz = %lld", n_rows, (long long)nnz);
+        std::vector<int32_t> rp, ci;
+        std::vector<double> va;
+        int rc = fetch_device(row_ptr, (size_t)n_rows + 1, rp, "row_ptr");
+        if (!rc) rc = fetch_device(col_idx, (size_t)nnz, ci, "col_idx");
+        if (!rc && (!params || params->format == SPMV_FORMAT_CSR)) {
+            // the plan needs the pattern alone: the values stay on the device
+            if (nnz > 0) rc = check_device(values, "values");
+            if (!rc) rc = validate_csr(n_rows, n_cols, nnz, rp.data(), nnz ? ci.data() : nullptr);
+            if (rc) return rc;
+            return create_csr(n_rows, n_cols, nnz, rp.data(), nnz ? ci.data() : nullptr, values, true, flags, params,
+                              out);
+        }
+        if (!rc) rc = fetch_device(values, (size_t)nnz, va, "values");
+        if (rc) return rc;
+        return spmv_create(n_rows, n_cols, nnz, rp.data(), nnz ? ci.data() : nullptr, nnz ? va.data() : nullptr,
+                           flags & ~SPMV_DEVICE_PTRS, params, out);
+    }
+    int rc = validate_csr(n_rows, n_cols, nnz, row_ptr, col_idx);
+    if (rc) return rc;
+    if (nnz > 0 && !values) return fail(SPMV_EINVAL, "values is NULL with nnz > 0");
+    if (params && params->format != SPMV_FORMAT_CSR) {
+        if (params->format != SPMV_FORMAT_SELL) return fail(SPMV_EINVAL, "format = %d unknown", params->format);
+        return create_sell(n_rows, n_cols, nnz, row_ptr, col_idx, values, flags, *params, out);
+    }
+    return create_csr(n_rows, n_cols, nnz, row_ptr, col_idx, values, false, flags, params, out);
 }
 
 extern "C" int spmv_destroy(spmv_matrix *A) {

@@ -5,7 +5,7 @@
 
 #include <cstdint>
 
-#include "jag_limits.h"
+#include "tile_limits.h"
 
 namespace spmvlib {
 
@@ -81,6 +81,14 @@ struct DevMatrix {
     int32_t n_jag_rest = 0;
     TileDesc *jag_rest = nullptr;    // direct-gather tiles of the rows in no jagged tile
     TileDesc *jag_long = nullptr;    // long_desc with the jagged product's partial numbers
+    // sweep tiles (sweep.hip), for the value types that have such a copy
+    int32_t n_sweep = 0, sweep_width = 0;
+    TileDesc *sweep_desc = nullptr;
+    uint16_t *sweep_place = nullptr; // per entry in sweep order: its place in the tile
+    int32_t *sweep_col = nullptr;
+    double *sweep64 = nullptr;
+    float *sweep32 = nullptr;
+    uint16_t *sweep16 = nullptr;
     bool xcd_remap = true;
     int32_t xcd_chunk_log2 = -1;     // XCD assignment (xcd_tile): -1 one contiguous range per XCD
     int32_t kernel = KV_AUTO;        // direct-gather kernel variant

@@ -2,12 +2,13 @@
 #pragma once
 
 #include <cstdint>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <utility>
 #include <vector>
 
-#include "jag_limits.h"
+#include "tile_limits.h"
 #include "spmv.h"
 
 namespace spmvlib {
@@ -127,6 +128,23 @@ struct JagPlan {
 // the long-row path either way.
 bool build_jag_plan(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *row_ptr, const int32_t *col_idx,
                     int long_len, JagPlan &J);
+
+// Sweep tiles (sweep.hip): consecutive rows of up to kSweepTile entries (no
+// long row among them), worked in order of column.  For scattered columns and
+// entries for a round of workgroups that nearly fill their CUs.
+constexpr int64_t kSweepMinNnz = int64_t(1) << 22;
+
+struct SweepPlan {
+    int32_t width = 0;            // entries of the largest tile
+    std::vector<int32_t> bound;   // first and end row per tile
+    size_t n = 0;                 // entries
+    std::unique_ptr<uint16_t[]> place;  // per entry in sweep order: its place in the tile
+};
+
+// The layout, or false where the gathers share cache lines or the matrix is
+// too small.
+bool build_sweep_plan(int32_t n_rows, int32_t n_cols, const int32_t *row_ptr, const int32_t *col_idx, int long_len,
+                      int n_cus, SweepPlan &S);
 
 // Sliced ELLPACK with sigma sorting (SELL-C-sigma; the paper's sliced
 // ELLPACK storage, Sec. 4.2, with C = 64 rows per slice, one per lane of a

@@ -1,7 +1,8 @@
 // Host-side layout of the jagged window tiles: which rows form tiles, each
 // tile's lanes in order of row length, its window's sectors, and its slices'
 // headers.  Pure C++ (no HIP calls); the positions and values are then
-// filled on the device from the CSR arrays.
+// filled on the device from the CSR arrays.  The same for the sweep tiles of
+// scattered orderings (sweep.hip).
 #include <algorithm>
 #include <atomic>
 #include <cstring>
@@ -164,6 +165,71 @@ bool build_jag_plan(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *
         if (stop > r) J.rest.emplace_back(r, stop);
         if (i < n_cand) r = first[i] + rows[i];
     }
+    return true;
+}
+
+// Distinct 128-byte lines of x per stored entry in blocks of 256 rows, over
+// about 32 blocks spread evenly (1: every gather a line of its own).
+static double lines_per_entry(int32_t n_rows, const int32_t *row_ptr, const int32_t *col_idx, int long_len) {
+    int64_t lines = 0, entries = 0;
+    std::vector<int32_t> u;
+    const int32_t blocks = (n_rows + 255) / 256, step = std::max(1, blocks / 32);
+    for (int32_t b = 0; b < blocks; b += step) {
+        u.clear();
+        for (int32_t r = b * 256; r < std::min(n_rows, b * 256 + 256); ++r)
+            if (row_ptr[r + 1] - row_ptr[r] <= long_len)
+                for (int32_t k = row_ptr[r]; k < row_ptr[r + 1]; ++k) u.push_back(col_idx[k] / 16);
+        entries += (int64_t)u.size();
+        std::sort(u.begin(), u.end());
+        lines += std::unique(u.begin(), u.end()) - u.begin();
+    }
+    return entries ? (double)lines / (double)entries : 0.0;
+}
+
+bool build_sweep_plan(int32_t n_rows, int32_t n_cols, const int32_t *row_ptr, const int32_t *col_idx, int long_len,
+                      int n_cus, SweepPlan &S) {
+    S = SweepPlan{};
+    if (lines_per_entry(n_rows, row_ptr, col_idx, long_len) < 0.75) return false;
+    const auto len_of = [row_ptr](int32_t r) { return row_ptr[r + 1] - row_ptr[r]; };
+    int64_t entries = 0;
+    for (int32_t r = 0; r < n_rows; ++r)
+        if (len_of(r) <= long_len) entries += len_of(r);
+    if (entries < kSweepMinNnz) return false;
+    // whole rounds of one workgroup per CU, each tile some rows short of full
+    const int64_t rounds = (entries + (int64_t)n_cus * 19500 - 1) / ((int64_t)n_cus * 19500);
+    const int32_t target = (int32_t)((entries + rounds * n_cus - 1) / (rounds * n_cus));
+    for (int32_t r = 0; r < n_rows;) {
+        if (len_of(r) > long_len) {
+            ++r;
+            continue;
+        }
+        const int32_t s = row_ptr[r];
+        int32_t r1 = r;
+        while (r1 < n_rows && len_of(r1) <= long_len && row_ptr[r1] - s < target && row_ptr[r1 + 1] - s <= kSweepTile)
+            ++r1;
+        S.bound.push_back(r);
+        S.bound.push_back(r1);
+        S.width = std::max(S.width, row_ptr[r1] - s);
+        r = r1;
+    }
+    const int32_t nt = (int32_t)(S.bound.size() / 2);
+    S.n = (size_t)row_ptr[n_rows];
+    S.place.reset(new uint16_t[S.n]);  // the long rows' parts stay unset and unread
+    // order of column, to 1/2048 of the columns' range (a stable counting
+    // sort per tile)
+    int shift = 0;
+    while (((int64_t)n_cols >> shift) > 2047) ++shift;
+    const int nth = std::max(1, std::min({32, (int)std::thread::hardware_concurrency(), nt / 8}));
+    run_shares(nth, [&](int t) {
+        int32_t at[2049];
+        for (int32_t i = (int32_t)((int64_t)nt * t / nth); i < (int32_t)((int64_t)nt * (t + 1) / nth); ++i) {
+            const int32_t s = row_ptr[S.bound[2 * i]], e = row_ptr[S.bound[2 * i + 1]];
+            std::memset(at, 0, sizeof at);
+            for (int32_t k = s; k < e; ++k) ++at[(col_idx[k] >> shift) + 1];
+            for (int b = 0; b < 2048; ++b) at[b + 1] += at[b];
+            for (int32_t k = s; k < e; ++k) S.place[(size_t)s + at[col_idx[k] >> shift]++] = (uint16_t)(k - s);
+        }
+    });
     return true;
 }
 

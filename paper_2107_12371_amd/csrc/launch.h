@@ -53,6 +53,14 @@ template <typename T> hipError_t launch_zero_fill(T *y, int64_t n, hipStream_t s
 // dynamic LDS.  Called once when a matrix with window blocks is created.
 hipError_t prepare_window_kernels();
 
+// dst[i] = src[i] rounded to binary32 (T = float) or, from there, to a
+// bfloat16 bit pattern (T = uint16_t; NaN kept quiet), to nearest even
+// (creation only).
+template <typename T> hipError_t launch_round_values(const double *src, T *dst, int64_t n, hipStream_t st);
+
+// The current device's CU count.
+int device_cus();
+
 // Caches the device's CU count and each kernel's occupancy so no runtime
 // query is made later (for example while a CG graph is being captured).
 void prepare_launch_queries();

@@ -41,6 +41,7 @@
 #include "launch.h"
 #include "sell.h"
 #include "spmv.h"
+#include "sweep.h"
 #include "tile.h"
 
 #include <algorithm>
@@ -482,7 +483,29 @@ template <typename T> __global__ __launch_bounds__(kBlock) void k_fill_zero(T *_
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) y[i] = T(0);
 }
 
+__device__ __forceinline__ void round_value(double d, float &o) { o = (float)d; }
+__device__ __forceinline__ void round_value(double d, uint16_t &o) {
+    const uint32_t u = __float_as_uint((float)d);
+    o = (u & 0x7fffffffu) > 0x7f800000u ? (uint16_t)((u >> 16) | 0x40u) : (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_round_values(const double *__restrict__ src, T *__restrict__ dst,
+                                                         int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock)
+        round_value(src[i], dst[i]);
+}
+
 // ---------------------------------------------------------------- launch
+
+template <typename T> hipError_t launch_round_values(const double *src, T *dst, int64_t n, hipStream_t st) {
+    if (n <= 0) return hipSuccess;
+    const int64_t blocks = std::min<int64_t>((n + kBlock - 1) / kBlock, 8192);
+    hipLaunchKernelGGL((k_round_values<T>), dim3((unsigned)blocks), dim3(kBlock), 0, st, src, dst, n);
+    return hipGetLastError();
+}
+template hipError_t launch_round_values<float>(const double *, float *, int64_t, hipStream_t);
+template hipError_t launch_round_values<uint16_t>(const double *, uint16_t *, int64_t, hipStream_t);
 
 template <typename T> hipError_t launch_zero_fill(T *y, int64_t n, hipStream_t st) {
     if (n <= 0) return hipSuccess;
@@ -542,6 +565,8 @@ static int cu_count() {
     return cus.load(std::memory_order_relaxed);
 }
 
+int device_cus() { return cu_count(); }
+
 // The product's own output as scratch for the long rows' piece sums: the
 // rows of the longest run without a long row, which the row-tile launches
 // of the same product write only after the long rows' launches (8-byte
@@ -600,6 +625,14 @@ static hipError_t launch_nt(const DevMatrix &M, SpmvArgs<V, X, Y> g, hipStream_t
         return hipGetLastError();
     }
     launch_long<V, X, Y, A, EPI>(M, g, M.long_desc, st);
+    if constexpr (EPI == EPI_PLAIN) {
+        // scattered orderings (the solvers' epilogues keep the row tiles)
+        const V *sv = sweep_pays<X>(M) ? sweep_values<V>(M) : nullptr;
+        if (sv) {
+            launch_sweep<V, X>(M, sv, g.x, g.y, g.done, st);
+            return hipGetLastError();
+        }
+    }
     if (M.n_stream > 0) {
         SpmvArgs<V, X, Y> a = g;
         a.desc = M.stream_desc;

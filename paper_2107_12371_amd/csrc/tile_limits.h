@@ -1,4 +1,4 @@
-// Limits of the jagged window tiles (host and device).
+// Limits of the jagged window tiles and of the sweep tiles (host and device).
 #pragma once
 
 namespace spmvlib {
@@ -7,4 +7,5 @@ constexpr int kJagMaxLen = 28;       // entries per row
 constexpr int kJagSector = 8;        // x words per window sector
 constexpr int kJagMaxSectors = 512;  // sectors per window: 4,096 words, 12-bit positions
 constexpr int kJagHdr = 16;          // header ints per slice
+constexpr int kSweepTile = 20480;    // entries per sweep tile: their FP64 products fill 160 KB of LDS
 }  // namespace spmvlib
