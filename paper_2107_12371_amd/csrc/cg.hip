@@ -15,10 +15,11 @@
 // update folded into this product's gathers), with the p.q partial in its
 // epilogue; and the x/r update, which writes p_new for its own rows beside
 // x and r, with the r.r partial, its workgroups each forming alpha from the
-// SpMV's partials.  Otherwise the p update is a launch of its own (three
-// launches), and with more than 4,096 SpMV partials or 1,024 r.r partials
-// that scalar takes a reduction launch of its own (five launches on the
-// largest systems).  All scalars live on the device;
+// SpMV's partials.  Otherwise it is three: the SpMV, the r update, whose
+// workgroups form alpha, and the update of x and p together, whose
+// workgroups form beta (so p is read once for both); with more than 4,096
+// SpMV partials their first-stage sums are a launch of their own (four).
+// All scalars live on the device;
 // every kernel returns at once when the device flag `done` is set, so a
 // captured graph of several iterations can be replayed blindly and the host
 // synchronises once per replay.  Reductions are two-stage with a fixed
@@ -64,6 +65,7 @@ struct CgState {
     double rho, rho_new, pq, alpha, beta, bb, tol2, rt2;
     double rr, omega;  // preconditioned CG: r.r of the iterate, polynomial weight
     int32_t iter, max_iter, done, flags;
+    int32_t step;  // the r update ran: the x/p update of the same iteration must run
 };
 
 // F_FRESH: the next fused product (k_spmv_pfused) takes beta from the state
@@ -74,7 +76,7 @@ struct CgState {
 // and never this one, so every workgroup reads the same value.
 enum : int32_t { F_CONVERGED = 1, F_BREAKDOWN = 2, F_MAXITER = 4, F_BADDIAG = 8, F_FRESH = 16 };
 enum : int {
-    R_BB = 0, R_RHO0 = 1, R_ALPHA = 2, R_BETA = 3, R_TRUE = 4, R_RR = 5, R_RZ = 6, R_RZ0 = 7, R_DIAG = 8,
+    R_BB = 0, R_RHO0 = 1, R_ALPHA = 2, R_TRUE = 4, R_RR = 5, R_RZ = 6, R_RZ0 = 7, R_DIAG = 8,
     R_BETA_DEFER = 9, R_RZ_DEFER = 10
 };
 
@@ -154,8 +156,7 @@ __device__ void apply_reduction(CgState *st, int mode, double t) {
                 st->done = 1;
             }
             break;
-        case R_BETA:
-        case R_BETA_DEFER:  // as R_BETA; rho is left to the next alpha step
+        case R_BETA_DEFER:  // beta from r.r; rho is left to the next alpha step
             st->rho_new = t;
             st->iter += 1;
             if (!isfinite(t)) {
@@ -166,7 +167,6 @@ __device__ void apply_reduction(CgState *st, int mode, double t) {
                 st->done = 1;
             } else {
                 st->beta = t / st->rho;
-                if (mode == R_BETA) st->rho = t;
                 if (st->iter >= st->max_iter) {
                     st->flags |= F_MAXITER;
                     st->done = 1;
@@ -178,7 +178,7 @@ __device__ void apply_reduction(CgState *st, int mode, double t) {
 
 __global__ __launch_bounds__(kBlock) void k_reduce(const double *__restrict__ part, int n, CgState *st, int mode) {
     __shared__ double sh[kBlock / kWave];
-    if ((mode == R_ALPHA || mode == R_BETA || mode == R_RR || mode == R_RZ) && st->done) return;
+    if ((mode == R_ALPHA || mode == R_RR || mode == R_RZ) && st->done) return;
     const double t = sum_partials(part, n, sh);
     if (threadIdx.x == 0) apply_reduction(st, mode, t);
 }
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce(const double *__restrict__ pa
 __global__ __launch_bounds__(kBlock) void k_reduce_stage(const double *__restrict__ part, int n, int chunk,
                                                          double *__restrict__ out, const CgState *st, int mode) {
     __shared__ double sh[kBlock / kWave];
-    if ((mode == R_ALPHA || mode == R_BETA || mode == R_RR || mode == R_RZ) && st->done) return;
+    if ((mode == R_ALPHA || mode == R_RR || mode == R_RZ) && st->done) return;
     const int lo = blockIdx.x * chunk, hi = min(n, lo + chunk);
     double s = 0.0;
 #pragma unroll 4
@@ -223,6 +223,7 @@ __global__ void k_init_state(CgState *st, double tol, int max_iter) {
     st->flags = 0;
     st->done = 0;
     st->alpha = st->beta = st->pq = st->rho_new = 0.0;
+    st->step = 0;
 }
 
 // alpha for the x/r update.  With n_pq >= 0 every workgroup forms p.q from
@@ -256,30 +257,134 @@ __device__ __forceinline__ bool form_alpha(CgState *st, const double *__restrict
     return true;
 }
 
-// x += alpha p, r -= alpha q and the r.r partial of each workgroup
+// r -= alpha q and the r.r partial of each workgroup; alpha = rho / p.q from
+// the SpMV's partials (or their first-stage sums), which every workgroup sums
+// in sum_partials' order.  The first rows of a lane are loaded before the
+// partials are waited for.  Workgroup 0 records the step for k_update_xp.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_update_xr(int n, int chunk, T *__restrict__ x, T *__restrict__ r,
-                                                      const T *__restrict__ p, const T *__restrict__ q,
-                                                      CgState *st, const double *__restrict__ part_pq, int n_pq,
-                                                      double *__restrict__ part) {
+__global__ __launch_bounds__(kBlock) void k_update_r(int n, int chunk, T *__restrict__ r, const T *__restrict__ q,
+                                                     CgState *st, const double *__restrict__ part_pq, int n_pq,
+                                                     double *__restrict__ part) {
+    constexpr int kRows = 4;
     __shared__ double sh[kBlock / kWave];
     __shared__ double pq_all;
-    if (st->done) return;
-    double alpha;
-    if (!form_alpha(st, part_pq, n_pq, sh, &pq_all, alpha)) return;
-    const T a = static_cast<T>(alpha);
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
     const int lo = blockIdx.x * chunk, hi = min(n, lo + chunk);
-    double d = 0.0;
-#pragma unroll 4
-    for (int i = lo + (int)threadIdx.x; i < hi; i += kBlock) {
-        const T xi = x[i] + a * p[i];
-        const T ri = r[i] - a * q[i];
-        x[i] = xi;
-        r[i] = ri;
-        d += static_cast<double>(ri) * static_cast<double>(ri);
+    const int done = st->done;
+    const double rho_new = st->rho_new;
+    T rs[kRows], qs[kRows];
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) {
+        const int i = min(lo + (int)threadIdx.x + u * kBlock, n - 1);
+        rs[u] = r[i];
+        qs[u] = q[i];
     }
-    const double t = block_sum(d, sh);
-    if (threadIdx.x == 0) part[blockIdx.x] = t;
+    double s = 0.0;
+#pragma unroll 4
+    for (int i = (int)threadIdx.x; i < n_pq; i += kBlock) s += part_pq[i];
+    if (done) {
+        if (first) st->step = 0;
+        return;
+    }
+    const double t = block_sum(s, sh);
+    if (threadIdx.x == 0) pq_all = t;
+    __syncthreads();
+    const double pq = pq_all;
+    const bool ok = pq > 0.0 && isfinite(pq);
+    if (first) st->step = ok ? 1 : 0;
+    if (!ok) {
+        if (first) apply_reduction(st, R_ALPHA, pq);
+        return;
+    }
+    const double alpha = rho_new / pq;
+    if (first) {
+        st->pq = pq;
+        st->alpha = alpha;
+        st->rho = rho_new;
+    }
+    const T a = static_cast<T>(alpha);
+    double d = 0.0;
+    for (int i0 = lo + (int)threadIdx.x;;) {
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            const int i = i0 + u * kBlock;
+            const T ri = rs[u] - a * qs[u];
+            if (i < hi) {
+                r[i] = ri;
+                d += static_cast<double>(ri) * static_cast<double>(ri);
+            }
+        }
+        i0 += kRows * kBlock;
+        if (i0 - (int)threadIdx.x >= hi) break;  // the same for every lane
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            const int i = min(i0 + u * kBlock, n - 1);
+            rs[u] = r[i];
+            qs[u] = q[i];
+        }
+    }
+    const double tt = block_sum(d, sh);
+    if (threadIdx.x == 0) part[blockIdx.x] = tt;
+}
+
+// x += alpha p, then p = r + beta p with beta = r.r / rho formed here: every
+// workgroup sums the r.r partials itself (sum_partials' order) and takes rho
+// from the state, which no workgroup writes in this launch.  Workgroup 0
+// records the iteration (R_BETA_DEFER: count, convergence, beta, rho_new);
+// the next alpha step copies rho_new to rho.  Whether the launch works is
+// told by `step`, set by k_update_r and not written here: `done` may be set
+// by workgroup 0 while others have yet to start, and their x must move too.
+// One pass over p serves both updates, and no reduction launch stands before
+// it or k_update_r: 4M rows in FP32, 27.6 us of updates (x and r together,
+// then p) and 9.4 us of one-workgroup reductions became 27.4 us (10.7 + 16.7).
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_update_xp(int n, int chunk, T *__restrict__ x, T *__restrict__ p,
+                                                      const T *__restrict__ r, CgState *st,
+                                                      const double *__restrict__ part, int n_part) {
+    constexpr int kRows = 4;
+    __shared__ double sh[kBlock / kWave];
+    __shared__ double rr_all;
+    const int lo = blockIdx.x * chunk, hi = min(n, lo + chunk);
+    const int step = st->step;
+    const double alpha = st->alpha, rho = st->rho, tol2 = st->tol2;
+    T xs[kRows], ps[kRows], rs[kRows];
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) {
+        const int i = min(lo + (int)threadIdx.x + u * kBlock, n - 1);
+        xs[u] = x[i];
+        ps[u] = p[i];
+        rs[u] = r[i];
+    }
+    double s = 0.0;
+#pragma unroll 4
+    for (int i = (int)threadIdx.x; i < n_part; i += kBlock) s += part[i];
+    if (!step) return;
+    const double t0 = block_sum(s, sh);
+    if (threadIdx.x == 0) rr_all = t0;
+    __syncthreads();
+    const double t = rr_all;
+    if (blockIdx.x == 0 && threadIdx.x == 0) apply_reduction(st, R_BETA_DEFER, t);
+    const bool more = isfinite(t) && t > tol2;  // else p is no longer read
+    const T a = static_cast<T>(alpha), b = static_cast<T>(t / rho);
+    for (int i0 = lo + (int)threadIdx.x;;) {
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            const int i = i0 + u * kBlock;
+            if (i < hi) {
+                x[i] = xs[u] + a * ps[u];
+                if (more) p[i] = rs[u] + b * ps[u];
+            }
+        }
+        i0 += kRows * kBlock;
+        if (i0 - (int)threadIdx.x >= hi) break;  // the same for every lane
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+            const int i = min(i0 + u * kBlock, n - 1);
+            xs[u] = x[i];
+            ps[u] = p[i];
+            rs[u] = r[i];
+        }
+    }
 }
 
 template <typename T>
@@ -287,33 +392,6 @@ __global__ __launch_bounds__(kBlock) void k_update_p(int n, T *__restrict__ p, c
                                                      const CgState *st) {
     if (st->done) return;
     const T b = static_cast<T>(st->beta);
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) p[i] = r[i] + b * p[i];
-}
-
-// p = r + beta p with beta formed in the same launch: when the x/r update
-// left few r.r partials, every workgroup sums them itself (sum_partials, the
-// order of the reduction launch) and takes beta = r.r / rho from the rho of
-// this iteration, which no workgroup writes here.  Workgroup 0 records the
-// step (R_BETA_DEFER: iteration count, convergence, beta, rho_new); the next
-// alpha step copies rho_new to rho.  The done flag is read at entry and set
-// here only where no workgroup updates p (converged, breakdown) or where p
-// is no longer read (the iteration cap).  Same beta, bit for bit, as the
-// reduction launch followed by k_update_p.
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_update_p_fold(int n, T *__restrict__ p, const T *__restrict__ r,
-                                                          CgState *st, const double *__restrict__ part,
-                                                          int n_part) {
-    __shared__ double sh[kBlock / kWave];
-    __shared__ double rr_all;
-    if (st->done) return;
-    const double t0 = sum_partials(part, n_part, sh);
-    if (threadIdx.x == 0) rr_all = t0;
-    __syncthreads();
-    const double t = rr_all;
-    const double rho = st->rho;
-    if (blockIdx.x == 0 && threadIdx.x == 0) apply_reduction(st, R_BETA_DEFER, t);
-    if (!isfinite(t) || t <= st->tol2) return;
-    const T b = static_cast<T>(t / rho);
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) p[i] = r[i] + b * p[i];
 }
 
@@ -330,7 +408,7 @@ __device__ __forceinline__ float fma_t(float a, float b, float c) { return __bui
 
 // The SpMV of a fused iteration: q = A p_new with p_new = r + beta p formed
 // for every gathered column and for the tile's own rows (the p.q partial of
-// the epilogue), exactly as k_update_p_fold forms it (fma(beta, p, r), beta
+// the epilogue), exactly as k_update_xp forms it (fma(beta, p, r), beta
 // rounded to T).  beta comes from the r.r partials, summed as
 // sum_partials sums them, and workgroup 0 records the step (R_BETA_DEFER),
 // unless F_FRESH hands beta over in the state.  On these small systems the
@@ -855,7 +933,7 @@ __global__ __launch_bounds__(kBlock) void k_update_xr_jacobi(int n, int chunk, d
 }
 
 // Preconditioned CG: p = z + beta p with the convergence test and beta
-// formed in the same launch, as k_update_p_fold does for plain CG: every
+// formed in the same launch, as k_update_xp does for plain CG: every
 // workgroup sums the r.r and r.z partials itself (the order of the
 // reduction launches) and workgroup 0 records the step (R_RR, then
 // R_RZ_DEFER), so no workgroup reads a field another writes here.
@@ -988,7 +1066,10 @@ template <typename T, typename V> struct CgCore {
     bool eager = false;
     // two launches per iteration (k_spmv_pfused + k_update_xpr): the
     // product is plain row tiles (no windows, no long rows) and every
-    // workgroup can sum the r.r partials itself
+    // workgroup can sum the r.r partials itself.  Matrices with jagged tiles
+    // take three: gathering p and r both through the row tiles costs more
+    // than the launch saved (27-point mesh, 125K rows 18.1 -> 15.4 us per
+    // iteration with jagged products, 422K rows 37.2 -> 27.4, 1M rows 74.1 -> 47.1)
     bool fused = false;
 
     CgCore(const DevMatrix &M_, const V *val_, int n_, hipStream_t s_) : M(M_), val(val_), n(n_), s(s_) {
@@ -998,7 +1079,7 @@ template <typename T, typename V> struct CgCore {
         n_part = n_partials<V>(M);
         fused = n_wg <= kFoldBeta && chunk <= 4 * kBlock && M.block == 1 && M.format == SPMV_FORMAT_CSR &&
                 M.n_stream > 0 &&
-                M.n_cwin == 0 && M.n_blk == 0 && M.n_long == 0 && M.n_seg == M.n_stream;
+                M.n_cwin == 0 && M.n_blk == 0 && M.n_long == 0 && M.n_seg == M.n_stream && !jag_values<V>(M);
     }
     ~CgCore() {
         if (!exec && !graph) return;
@@ -1032,6 +1113,21 @@ template <typename T, typename V> struct CgCore {
         hipLaunchKernelGGL(k_reduce, dim3(1), dim3(kBlock), 0, t, part2, nb, st, mode);
     }
 
+    // What the workgroups of the r update sum to p.q: the SpMV's partials, or
+    // the first-stage sums of more than kFoldAlpha of them (the sums that
+    // reduce() takes, in its order).
+    const double *pq_partials(int *n_out, hipStream_t t) {
+        if (n_part <= kFoldAlpha) {
+            *n_out = n_part;
+            return part_seg;
+        }
+        const int chunk = (n_part + kStage1 - 1) / kStage1;
+        *n_out = (n_part + chunk - 1) / chunk;
+        hipLaunchKernelGGL(k_reduce_stage, dim3(*n_out), dim3(kBlock), 0, t, part_seg, n_part, chunk, part2, st,
+                           (int)R_ALPHA);
+        return part2;
+    }
+
     template <int NT> void launch_pfused_nt(hipStream_t t, int per_xcd, int grid) {
         hipLaunchKernelGGL((k_spmv_pfused<T, V, NT>), dim3(grid), dim3(kBlock), 0, t, M.stream_desc, M.n_stream,
                            per_xcd, M.xcd_chunk_log2, M.row_ptr, M.col, val, p, r, q, part_seg, st, part_vec, n_wg);
@@ -1058,17 +1154,10 @@ template <typename T, typename V> struct CgCore {
         const int *done = &st->done;
         hipError_t e = launch_spmv<V, T, T, T>(M, val, p, q, EPI_DOT, nullptr, part_seg, done, t, long_ws);
         if (e != hipSuccess) return e;
-        const bool fold_alpha = n_part <= kFoldAlpha;
-        if (!fold_alpha) reduce(part_seg, n_part, R_ALPHA, t);
-        hipLaunchKernelGGL((k_update_xr<T>), dim3(n_wg), dim3(kBlock), 0, t, n, chunk, x, r, p, q, st, part_seg,
-                           fold_alpha ? n_part : -1, part_vec);
-        if (n_wg <= kFoldBeta) {
-            hipLaunchKernelGGL((k_update_p_fold<T>), dim3(grid_for(n)), dim3(kBlock), 0, t, n, p, r, st, part_vec,
-                               n_wg);
-        } else {
-            reduce(part_vec, n_wg, R_BETA, t);
-            hipLaunchKernelGGL((k_update_p<T>), dim3(grid_for(n)), dim3(kBlock), 0, t, n, p, r, st);
-        }
+        int n_pq = 0;
+        const double *pq = pq_partials(&n_pq, t);
+        hipLaunchKernelGGL((k_update_r<T>), dim3(n_wg), dim3(kBlock), 0, t, n, chunk, r, q, st, pq, n_pq, part_vec);
+        hipLaunchKernelGGL((k_update_xp<T>), dim3(n_wg), dim3(kBlock), 0, t, n, chunk, x, p, r, st, part_vec, n_wg);
         return hipGetLastError();
     }
 
