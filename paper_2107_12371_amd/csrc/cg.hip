@@ -76,7 +76,7 @@ struct CgState {
 // and never this one, so every workgroup reads the same value.
 enum : int32_t { F_CONVERGED = 1, F_BREAKDOWN = 2, F_MAXITER = 4, F_BADDIAG = 8, F_FRESH = 16 };
 enum : int {
-    R_BB = 0, R_RHO0 = 1, R_ALPHA = 2, R_TRUE = 4, R_RR = 5, R_RZ = 6, R_RZ0 = 7, R_DIAG = 8,
+    R_BB = 0, R_RHO0 = 1, R_ALPHA = 2, R_TRUE = 4, R_RR = 5, R_RZ0 = 7, R_DIAG = 8,
     R_BETA_DEFER = 9, R_RZ_DEFER = 10
 };
 
@@ -123,14 +123,12 @@ __device__ void apply_reduction(CgState *st, int mode, double t) {
                 st->done = 1;
             }
             break;
-        case R_RZ:  // preconditioned CG, after z = M^-1 r: beta from r.z
-        case R_RZ_DEFER:  // as R_RZ; rho is left to the next alpha step
+        case R_RZ_DEFER:  // preconditioned CG, after z = M^-1 r: beta from r.z; rho is left to the next alpha step
             if (!(t > 0.0) || !isfinite(t)) {
                 st->flags |= F_BREAKDOWN;
                 st->done = 1;
             } else {
                 st->beta = t / st->rho;
-                if (mode == R_RZ) st->rho = t;
                 st->rho_new = t;
                 if (st->iter >= st->max_iter) {
                     st->flags |= F_MAXITER;
@@ -178,7 +176,7 @@ __device__ void apply_reduction(CgState *st, int mode, double t) {
 
 __global__ __launch_bounds__(kBlock) void k_reduce(const double *__restrict__ part, int n, CgState *st, int mode) {
     __shared__ double sh[kBlock / kWave];
-    if ((mode == R_ALPHA || mode == R_RR || mode == R_RZ) && st->done) return;
+    if (mode == R_ALPHA && st->done) return;
     const double t = sum_partials(part, n, sh);
     if (threadIdx.x == 0) apply_reduction(st, mode, t);
 }
@@ -188,7 +186,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce(const double *__restrict__ pa
 __global__ __launch_bounds__(kBlock) void k_reduce_stage(const double *__restrict__ part, int n, int chunk,
                                                          double *__restrict__ out, const CgState *st, int mode) {
     __shared__ double sh[kBlock / kWave];
-    if ((mode == R_ALPHA || mode == R_RR || mode == R_RZ) && st->done) return;
+    if (mode == R_ALPHA && st->done) return;
     const int lo = blockIdx.x * chunk, hi = min(n, lo + chunk);
     double s = 0.0;
 #pragma unroll 4
@@ -226,20 +224,14 @@ __global__ void k_init_state(CgState *st, double tol, int max_iter) {
     st->step = 0;
 }
 
-// alpha for the x/r update.  With n_pq >= 0 every workgroup forms p.q from
-// the SpMV's n_pq partials itself (few partials: cheaper than a reduction
-// launch) and alpha = rho / p.q from it; with n_pq < 0 alpha was formed by a
-// reduction launch.  The sum is sum_partials over the same partials as that
-// launch, so the iterates are bit for bit the same.  Returns false on a p.q
-// breakdown, which every workgroup detects alike and workgroup 0 records;
-// the state's done flag is read once at kernel entry, and within a launch
-// only that record sets it.
+// alpha for the preconditioned x/r updates: every workgroup sums the n_pq
+// values (the SpMV's partials or their first-stage sums) in sum_partials'
+// order and takes alpha = rho / p.q, cheaper than a reduction launch.
+// Returns false on a p.q breakdown, which every workgroup detects alike and
+// workgroup 0 records; the state's done flag is read once at kernel entry,
+// and within a launch only that record sets it.
 __device__ __forceinline__ bool form_alpha(CgState *st, const double *__restrict__ part_pq, int n_pq, double *sh,
                                            double *pq_all, double &alpha) {
-    if (n_pq < 0) {
-        alpha = st->alpha;
-        return true;
-    }
     const double t = sum_partials(part_pq, n_pq, sh);
     if (threadIdx.x == 0) *pq_all = t;
     __syncthreads();
@@ -261,23 +253,26 @@ __device__ __forceinline__ bool form_alpha(CgState *st, const double *__restrict
 // the SpMV's partials (or their first-stage sums), which every workgroup sums
 // in sum_partials' order.  The first rows of a lane are loaded before the
 // partials are waited for.  Workgroup 0 records the step for k_update_xp.
-template <typename T>
+// JACOBI: also the r.z partials, z = D^-1 r.
+template <typename T, bool JACOBI>
 __global__ __launch_bounds__(kBlock) void k_update_r(int n, int chunk, T *__restrict__ r, const T *__restrict__ q,
-                                                     CgState *st, const double *__restrict__ part_pq, int n_pq,
-                                                     double *__restrict__ part) {
+                                                     const T *__restrict__ dinv, CgState *st,
+                                                     const double *__restrict__ part_pq, int n_pq,
+                                                     double *__restrict__ part, double *__restrict__ part_rz) {
     constexpr int kRows = 4;
-    __shared__ double sh[kBlock / kWave];
+    __shared__ double sh[kBlock / kWave], sh2[kBlock / kWave];
     __shared__ double pq_all;
     const bool first = blockIdx.x == 0 && threadIdx.x == 0;
     const int lo = blockIdx.x * chunk, hi = min(n, lo + chunk);
     const int done = st->done;
     const double rho_new = st->rho_new;
-    T rs[kRows], qs[kRows];
+    T rs[kRows], qs[kRows], ds[kRows];
 #pragma unroll
     for (int u = 0; u < kRows; ++u) {
         const int i = min(lo + (int)threadIdx.x + u * kBlock, n - 1);
         rs[u] = r[i];
         qs[u] = q[i];
+        if (JACOBI) ds[u] = dinv[i];
     }
     double s = 0.0;
 #pragma unroll 4
@@ -303,7 +298,7 @@ __global__ __launch_bounds__(kBlock) void k_update_r(int n, int chunk, T *__rest
         st->rho = rho_new;
     }
     const T a = static_cast<T>(alpha);
-    double d = 0.0;
+    double d = 0.0, dz = 0.0;
     for (int i0 = lo + (int)threadIdx.x;;) {
 #pragma unroll
         for (int u = 0; u < kRows; ++u) {
@@ -312,6 +307,7 @@ __global__ __launch_bounds__(kBlock) void k_update_r(int n, int chunk, T *__rest
             if (i < hi) {
                 r[i] = ri;
                 d += static_cast<double>(ri) * static_cast<double>(ri);
+                if (JACOBI) dz += static_cast<double>(ri) * static_cast<double>(ds[u] * ri);
             }
         }
         i0 += kRows * kBlock;
@@ -321,10 +317,15 @@ __global__ __launch_bounds__(kBlock) void k_update_r(int n, int chunk, T *__rest
             const int i = min(i0 + u * kBlock, n - 1);
             rs[u] = r[i];
             qs[u] = q[i];
+            if (JACOBI) ds[u] = dinv[i];
         }
     }
     const double tt = block_sum(d, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = tt;
+    if (JACOBI) {
+        const double tz = block_sum(dz, sh2);
+        if (threadIdx.x == 0) part_rz[blockIdx.x] = tz;
+    }
 }
 
 // x += alpha p, then p = r + beta p with beta = r.r / rho formed here: every
@@ -337,42 +338,57 @@ __global__ __launch_bounds__(kBlock) void k_update_r(int n, int chunk, T *__rest
 // One pass over p serves both updates, and no reduction launch stands before
 // it or k_update_r: 4M rows in FP32, 27.6 us of updates (x and r together,
 // then p) and 9.4 us of one-workgroup reductions became 27.4 us (10.7 + 16.7).
-template <typename T>
+// JACOBI: p = z + beta p with z = D^-1 r formed again here and beta = r.z / rho;
+// z is never stored.
+template <typename T, bool JACOBI>
 __global__ __launch_bounds__(kBlock) void k_update_xp(int n, int chunk, T *__restrict__ x, T *__restrict__ p,
-                                                      const T *__restrict__ r, CgState *st,
-                                                      const double *__restrict__ part, int n_part) {
+                                                      const T *__restrict__ r, const T *__restrict__ dinv,
+                                                      CgState *st, const double *__restrict__ part,
+                                                      const double *__restrict__ part_rz, int n_part) {
     constexpr int kRows = 4;
-    __shared__ double sh[kBlock / kWave];
-    __shared__ double rr_all;
+    __shared__ double sh[kBlock / kWave], sh2[kBlock / kWave];
+    __shared__ double rr_all, rz_all;
     const int lo = blockIdx.x * chunk, hi = min(n, lo + chunk);
     const int step = st->step;
     const double alpha = st->alpha, rho = st->rho, tol2 = st->tol2;
-    T xs[kRows], ps[kRows], rs[kRows];
+    T xs[kRows], ps[kRows], rs[kRows], ds[kRows];
 #pragma unroll
     for (int u = 0; u < kRows; ++u) {
         const int i = min(lo + (int)threadIdx.x + u * kBlock, n - 1);
         xs[u] = x[i];
         ps[u] = p[i];
         rs[u] = r[i];
+        if (JACOBI) ds[u] = dinv[i];
     }
-    double s = 0.0;
+    double s = 0.0, sz = 0.0;
 #pragma unroll 4
-    for (int i = (int)threadIdx.x; i < n_part; i += kBlock) s += part[i];
+    for (int i = (int)threadIdx.x; i < n_part; i += kBlock) {
+        s += part[i];
+        if (JACOBI) sz += part_rz[i];
+    }
     if (!step) return;
     const double t0 = block_sum(s, sh);
-    if (threadIdx.x == 0) rr_all = t0;
+    const double z0 = JACOBI ? block_sum(sz, sh2) : 0.0;
+    if (threadIdx.x == 0) {
+        rr_all = t0;
+        rz_all = z0;
+    }
     __syncthreads();
-    const double t = rr_all;
-    if (blockIdx.x == 0 && threadIdx.x == 0) apply_reduction(st, R_BETA_DEFER, t);
-    const bool more = isfinite(t) && t > tol2;  // else p is no longer read
-    const T a = static_cast<T>(alpha), b = static_cast<T>(t / rho);
+    const double t = rr_all, tz = rz_all;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        apply_reduction(st, JACOBI ? R_RR : R_BETA_DEFER, t);
+        if (JACOBI && !st->done) apply_reduction(st, R_RZ_DEFER, tz);
+    }
+    // false: p is no longer read
+    const bool more = isfinite(t) && t > tol2 && (!JACOBI || (tz > 0.0 && isfinite(tz)));
+    const T a = static_cast<T>(alpha), b = static_cast<T>((JACOBI ? tz : t) / rho);
     for (int i0 = lo + (int)threadIdx.x;;) {
 #pragma unroll
         for (int u = 0; u < kRows; ++u) {
             const int i = i0 + u * kBlock;
             if (i < hi) {
                 x[i] = xs[u] + a * ps[u];
-                if (more) p[i] = rs[u] + b * ps[u];
+                if (more) p[i] = (JACOBI ? ds[u] * rs[u] : rs[u]) + b * ps[u];
             }
         }
         i0 += kRows * kBlock;
@@ -383,16 +399,9 @@ __global__ __launch_bounds__(kBlock) void k_update_xp(int n, int chunk, T *__res
             xs[u] = x[i];
             ps[u] = p[i];
             rs[u] = r[i];
+            if (JACOBI) ds[u] = dinv[i];
         }
     }
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_update_p(int n, T *__restrict__ p, const T *__restrict__ r,
-                                                     const CgState *st) {
-    if (st->done) return;
-    const T b = static_cast<T>(st->beta);
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) p[i] = r[i] + b * p[i];
 }
 
 // Unconditional p = r + beta p (used after a residual replacement).
@@ -830,7 +839,7 @@ __global__ __launch_bounds__(kBlock) void k_dinv_f32(int n, float *__restrict__ 
 }
 
 // x += alpha p; r -= alpha q; t = D^-1 r (FP32); partial r.r (alpha formed
-// here on small systems, as in k_update_xr)
+// here, form_alpha)
 __global__ __launch_bounds__(kBlock) void k_update_xr_pcg(int n, int chunk, double *__restrict__ x,
                                                           double *__restrict__ r, const double *__restrict__ p,
                                                           const double *__restrict__ q,
@@ -879,11 +888,10 @@ __global__ __launch_bounds__(kBlock) void k_precond_z(int n, int chunk, const do
 
 // ------------------------------------------- preconditioned CG (Jacobi)
 //
-// M = D = diag(A): z = D^-1 r is fused into the x/r update, and r.r and r.z
-// are reduced together, so an iteration takes the launches of plain CG
-// (SpMV + p.q; x/r/z update, with alpha formed in it on small systems; the
-// r.r / r.z reduction that forms the convergence flag and beta, folded into
-// the p update on small systems; p update).
+// M = D = diag(A): z = D^-1 r is formed where it is used and never stored, and
+// r.r and r.z are reduced together, so an iteration takes the launches of
+// plain CG (SpMV + p.q; r update, with alpha formed in it; x/p update, with
+// the convergence flag and beta formed in it).
 
 // Per workgroup: how many entries of v are NaN (k_diag_inv marks a diagonal
 // that is not positive and finite so).
@@ -897,42 +905,7 @@ __global__ __launch_bounds__(kBlock) void k_count_nan(int n, int chunk, const do
     if (threadIdx.x == 0) part[blockIdx.x] = t;
 }
 
-// x += alpha p; r -= alpha q; z = D^-1 r; partials r.r and r.z
-__global__ __launch_bounds__(kBlock) void k_update_xr_jacobi(int n, int chunk, double *__restrict__ x,
-                                                             double *__restrict__ r, const double *__restrict__ p,
-                                                             const double *__restrict__ q,
-                                                             const double *__restrict__ dinv,
-                                                             double *__restrict__ z, CgState *st,
-                                                             const double *__restrict__ part_pq, int n_pq,
-                                                             double *__restrict__ part_rr,
-                                                             double *__restrict__ part_rz) {
-    __shared__ double sh[kBlock / kWave], sh2[kBlock / kWave];
-    __shared__ double pq_all;
-    if (st->done) return;
-    double a;
-    if (!form_alpha(st, part_pq, n_pq, sh, &pq_all, a)) return;
-    const int lo = blockIdx.x * chunk, hi = min(n, lo + chunk);
-    double drr = 0.0, drz = 0.0;
-#pragma unroll 4
-    for (int i = lo + (int)threadIdx.x; i < hi; i += kBlock) {
-        const double xi = x[i] + a * p[i];
-        const double ri = r[i] - a * q[i];
-        const double zi = dinv[i] * ri;
-        x[i] = xi;
-        r[i] = ri;
-        z[i] = zi;
-        drr += ri * ri;
-        drz += ri * zi;
-    }
-    const double trr = block_sum(drr, sh);
-    const double trz = block_sum(drz, sh2);
-    if (threadIdx.x == 0) {
-        part_rr[blockIdx.x] = trr;
-        part_rz[blockIdx.x] = trz;
-    }
-}
-
-// Preconditioned CG: p = z + beta p with the convergence test and beta
+// Polynomial preconditioner: p = z + beta p with the convergence test and beta
 // formed in the same launch, as k_update_xp does for plain CG: every
 // workgroup sums the r.r and r.z partials itself (the order of the
 // reduction launches) and workgroup 0 records the step (R_RR, then
@@ -977,19 +950,6 @@ __global__ __launch_bounds__(kBlock) void k_precond_jacobi(int n, int chunk, con
     }
     const double t = block_sum(d, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = t;
-}
-
-// The convergence test on r.r, then (unless it stopped) beta from r.z: the
-// two reductions k_reduce makes with R_RR and R_RZ, in one launch.
-__global__ __launch_bounds__(kBlock) void k_reduce_rr_rz(const double *__restrict__ part_rr,
-                                                         const double *__restrict__ part_rz, int n, CgState *st) {
-    __shared__ double sh[kBlock / kWave], sh2[kBlock / kWave];
-    if (st->done) return;
-    const double trr = sum_partials(part_rr, n, sh);
-    const double trz = sum_partials(part_rz, n, sh2);
-    if (threadIdx.x != 0) return;
-    apply_reduction(st, R_RR, trr);
-    if (!st->done) apply_reduction(st, R_RZ, trz);
 }
 
 // ------------------------------------------------------------ host driver
@@ -1092,15 +1052,14 @@ template <typename T, typename V> struct CgCore {
     // workgroup for up to 4096 partials, else a fixed-partition first stage
     // over up to kStage1 workgroups and a one-workgroup second stage.
     static constexpr int kStage1 = 256;
-    // Up to this many SpMV partials every workgroup of the x/r update sums
+    // Up to this many SpMV partials every workgroup of the r update sums
     // them itself instead of waiting for a reduction launch (4,096: 398K and
     // 775K rows, 1,920 and 3,745 tiles, 6% and 4% faster per iteration than
     // with a reduction launch; k_reduce sums up to 4,096 partials in the
     // same order, so alpha has the same bits either way).
     static constexpr int kFoldAlpha = 4096;
-    // Up to this many r.r partials (systems up to 1,048,576 rows) every
-    // workgroup of the p update forms beta itself (measured: -7% per
-    // iteration at 398,000 rows, -1.5% at 775,058).
+    // Up to this many r.r partials (systems up to 1,048,576 rows) the fused
+    // product, whose workgroups each sum them, may take the p update over.
     static constexpr int kFoldBeta = 1024;
     void reduce(const double *part, int n, int mode, hipStream_t t) {
         if (n <= 4096) {
@@ -1156,8 +1115,10 @@ template <typename T, typename V> struct CgCore {
         if (e != hipSuccess) return e;
         int n_pq = 0;
         const double *pq = pq_partials(&n_pq, t);
-        hipLaunchKernelGGL((k_update_r<T>), dim3(n_wg), dim3(kBlock), 0, t, n, chunk, r, q, st, pq, n_pq, part_vec);
-        hipLaunchKernelGGL((k_update_xp<T>), dim3(n_wg), dim3(kBlock), 0, t, n, chunk, x, p, r, st, part_vec, n_wg);
+        hipLaunchKernelGGL((k_update_r<T, false>), dim3(n_wg), dim3(kBlock), 0, t, n, chunk, r, q,
+                           static_cast<const T *>(nullptr), st, pq, n_pq, part_vec, static_cast<double *>(nullptr));
+        hipLaunchKernelGGL((k_update_xp<T, false>), dim3(n_wg), dim3(kBlock), 0, t, n, chunk, x, p, r,
+                           static_cast<const T *>(nullptr), st, part_vec, static_cast<const double *>(nullptr), n_wg);
         return hipGetLastError();
     }
 
@@ -1290,11 +1251,13 @@ int alloc_core(Buffers &B, CgCore<T, V> &C) {
 
 // Preconditioned CG: CgCore's buffers and reductions plus z and D^-1, and
 // for the bfloat16 polynomial preconditioner the FP32 vectors of its
-// product.  Polynomial: eight launches per iteration on the largest systems
-// (SpMV + p.q, alpha, x/r update + r.r + t = D^-1 r, convergence, bfloat16
-// SpMV, z + r.z, beta, p update), five on small ones, where alpha is formed
-// in the x/r update and the convergence test and beta in the p update.
-// Jacobi: three to five (see its kernels).
+// product.  Polynomial: five launches per iteration (SpMV + p.q; x/r update
+// + r.r + t = D^-1 r, with alpha formed in it; bfloat16 SpMV; z + r.z; p update,
+// with the convergence test and beta formed in it); Jacobi: three (SpMV +
+// p.q; r update; x/p update).  One more with over 4,096 SpMV partials, whose
+// first-stage sums are a launch of their own.  One-workgroup reduction
+// launches between them (three and two more on systems above 1M rows) cost
+// 4.7 us each.
 struct PcgCore : CgCore<double, double> {
     double *z = nullptr, *dinv = nullptr, *part_rz = nullptr;
     float *t = nullptr, *sv = nullptr;
@@ -1310,39 +1273,26 @@ struct PcgCore : CgCore<double, double> {
         hipError_t e = launch_spmv<double, double, double, double>(M, val, p, q, EPI_DOT, nullptr, part_seg, done, ts,
                                                                      long_ws);
         if (e != hipSuccess) return e;
+        int n_pq = 0;
+        const double *pq = pq_partials(&n_pq, ts);
         if (jacobi) {
-            const bool fold_alpha = n_part <= kFoldAlpha;
-            if (!fold_alpha) reduce(part_seg, n_part, R_ALPHA, ts);
-            hipLaunchKernelGGL(k_update_xr_jacobi, dim3(n_wg), dim3(kBlock), 0, ts, n, chunk, x, r, p, q, dinv, z,
-                               st, part_seg, fold_alpha ? n_part : -1, part_vec, part_rz);
-            if (n_wg <= kFoldBeta) {
-                hipLaunchKernelGGL(k_update_p_pcg, dim3(grid_for(n)), dim3(kBlock), 0, ts, n, p, z, st, part_vec,
-                                   part_rz, n_wg);
-            } else {
-                hipLaunchKernelGGL(k_reduce_rr_rz, dim3(1), dim3(kBlock), 0, ts, part_vec, part_rz, n_wg, st);
-                hipLaunchKernelGGL((k_update_p<double>), dim3(grid_for(n)), dim3(kBlock), 0, ts, n, p, z, st);
-            }
+            hipLaunchKernelGGL((k_update_r<double, true>), dim3(n_wg), dim3(kBlock), 0, ts, n, chunk, r, q, dinv, st,
+                               pq, n_pq, part_vec, part_rz);
+            hipLaunchKernelGGL((k_update_xp<double, true>), dim3(n_wg), dim3(kBlock), 0, ts, n, chunk, x, p, r, dinv,
+                               st, part_vec, part_rz, n_wg);
             return hipGetLastError();
         }
-        const bool fold_alpha = n_part <= kFoldAlpha, fold_beta = n_wg <= kFoldBeta;
-        if (!fold_alpha) reduce(part_seg, n_part, R_ALPHA, ts);
-        hipLaunchKernelGGL(k_update_xr_pcg, dim3(n_wg), dim3(kBlock), 0, ts, n, chunk, x, r, p, q, dinv, t, st,
-                           part_seg, fold_alpha ? n_part : -1, part_vec);
-        // folded: the convergence test waits for the p update, so on the last
-        // iteration the preconditioner runs once more (it writes neither x nor r)
-        if (!fold_beta) reduce(part_vec, n_wg, R_RR, ts);
+        const int p_grid = std::min(grid_for(n), 2048);
+        hipLaunchKernelGGL(k_update_xr_pcg, dim3(n_wg), dim3(kBlock), 0, ts, n, chunk, x, r, p, q, dinv, t, st, pq,
+                           n_pq, part_vec);
+        // the convergence test waits for the p update, so on the last
+        // iteration the preconditioner runs once more (it writes neither x
+        // nor r)
         e = launch_spmv<uint16_t, float, float, float>(M, M.val16, t, sv, EPI_PLAIN, nullptr, nullptr, done, ts,
                                                           long_ws);
         if (e != hipSuccess) return e;
-        double *rz = fold_beta ? part_rz : part_vec;
-        hipLaunchKernelGGL(k_precond_z, dim3(n_wg), dim3(kBlock), 0, ts, n, chunk, r, sv, dinv, z, st, rz, 0);
-        if (fold_beta) {
-            hipLaunchKernelGGL(k_update_p_pcg, dim3(grid_for(n)), dim3(kBlock), 0, ts, n, p, z, st, part_vec,
-                               part_rz, n_wg);
-        } else {
-            reduce(part_vec, n_wg, R_RZ, ts);
-            hipLaunchKernelGGL((k_update_p<double>), dim3(grid_for(n)), dim3(kBlock), 0, ts, n, p, z, st);
-        }
+        hipLaunchKernelGGL(k_precond_z, dim3(n_wg), dim3(kBlock), 0, ts, n, chunk, r, sv, dinv, z, st, part_rz, 0);
+        hipLaunchKernelGGL(k_update_p_pcg, dim3(p_grid), dim3(kBlock), 0, ts, n, p, z, st, part_vec, part_rz, n_wg);
         return hipGetLastError();
     }
 
