@@ -219,6 +219,33 @@ static int apply_typed(const spmv_matrix *A, const V *val, const X *x, Y *y, voi
     return SPMV_OK;
 }
 
+// The k-vector product's tiles: the rows outside the long ones, cut to both
+// limits of kSpmmEntries.
+static int upload_spmm(Uploader &U, DevMatrix &M, const Plan &P, const int32_t *row_ptr) {
+    for (int l = 0; l < 2; ++l) {
+        SpmmTiles &T = M.spmm[l];
+        std::vector<TileDesc> v;
+        for (int32_t sg = 0; sg < P.n_seg(); ++sg) {
+            if (P.seg_kind[sg] == SEG_LONG) continue;
+            const int32_t end = P.seg_bound[sg + 1];
+            for (int32_t r = P.seg_bound[sg]; r < end;) {
+                TileDesc d{};
+                d.r0 = r++;
+                while (r < end && r - d.r0 < kSpmmRows && row_ptr[r + 1] - row_ptr[d.r0] <= kSpmmEntries[l]) ++r;
+                d.r1 = r;
+                d.s = row_ptr[d.r0];
+                d.e = row_ptr[d.r1];
+                T.entries = std::max(T.entries, d.e - d.s);
+                v.push_back(d);
+            }
+        }
+        T.n = (int32_t)v.size();
+        if (v.empty()) continue;
+        if (int rc = U.put(&T.desc, v.data(), v.size(), 0)) return rc;
+    }
+    return SPMV_OK;
+}
+
 // The jagged tiles' arrays, for the value types in `fp64` and the handle's
 // FP32 / BF16 copies.
 static int upload_jag(Uploader &U, DevMatrix &M, const JagPlan &J, const int32_t *row_ptr,
@@ -574,6 +601,7 @@ static int create_csr(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t
         if (P.seg_kind[sg] != SEG_LONG)
             A->max_tile_entries = std::max(A->max_tile_entries,
                                            row_ptr[P.seg_bound[sg + 1]] - row_ptr[P.seg_bound[sg]]);
+    if (!rc) rc = upload_spmm(U, M, P, row_ptr);
     if (!rc) add_layouts(U, M, row_ptr, col_idx, params, d);
     if (!rc) prepare_launch_queries();
     if (!rc && M.n_blk) {

@@ -18,6 +18,11 @@ constexpr int kCwinMaxRunsDev = 64; // compact windows: runs per tile (plan limi
 // (one workgroup's share when the pieces of a row run side by side).
 constexpr int kLongPiece = 16384;
 
+// Tiles of the k-vector product: up to so many entries (a longer row is a tile
+// of its own) and rows.
+constexpr int kSpmmEntries[2] = {1024, 2048};
+constexpr int kSpmmRows = 512;
+
 // Epilogues of the row-tile kernels.
 enum Epilogue : int {
     EPI_PLAIN = 0,  // y_i = (A x)_i
@@ -37,6 +42,11 @@ struct TileDesc {
 
 // Kernel variants for the direct-gather tiles.
 enum KernelVariant : int32_t { KV_AUTO = 0, KV_ONE_TILE = 1, KV_PIPELINED = 2, KV_WAVE = 3 };
+
+struct SpmmTiles {
+    int32_t n = 0, entries = 0;  // and the entries of the largest
+    TileDesc *desc = nullptr;
+};
 
 // Resident matrix and its plan in device memory.  Owned by spmv_matrix.
 struct DevMatrix {
@@ -68,6 +78,7 @@ struct DevMatrix {
     int32_t *runs = nullptr;         // (first column, window position) per run
     uint16_t *lidx = nullptr;        // window-relative column per stored entry (+ padding)
     uint32_t *lidx12 = nullptr;      // 2048-entry tiles: packed 12-bit positions per tile and lane
+    SpmmTiles spmm[2];               // tiles of the k-vector product (spmm.hip)
     // jagged window tiles (jag.hip), for the value types that have a copy of
     // the values in that order
     int32_t n_jag = 0, jag_stride = 0, jag_width = 0, jag_groups = 0;

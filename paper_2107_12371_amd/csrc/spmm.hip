@@ -2,12 +2,13 @@
 // (the k values of one row contiguous), so one gather of X's row c brings
 // all the columns a lane works on.
 //
-// One workgroup per row tile of the handle's plan (direct, compact-window
-// and ring tiles alike; only the tile's rows and stored entries are used).
-// The tile's values and column indices are staged in LDS with coalesced
-// loads; then the lanes take (row, column group) tasks: a lane walks its
-// row's entries in ascending order, U entries per round with all their
-// gathers of KC adjacent values of X issued before any is used, and adds
+// One workgroup per tile of up to 1,024 or 2,048 stored entries (the rows
+// outside the handle's long rows, whatever kernel its plan gives the
+// single-vector product).  The tile's values, column indices and row bounds are
+// staged in LDS with coalesced loads; then the lanes take (row, column group)
+// tasks: a lane walks its row's entries in ascending order, U entries per round
+// with all their gathers of KC adjacent values of X issued before any is used,
+// and adds
 // the rounded products one by one starting from zero, exactly as the
 // single-vector product sums a row, so column j of Y equals the
 // single-vector product of column j of X bit for bit.  A row longer than a
@@ -17,8 +18,7 @@
 // workgroup per (row, column) walking the pieces.
 // The values are read once for all k columns, which is what the batched
 // requests of a serving workload need.  One column goes to the
-// single-vector product.  Measured on the 16M-row mesh matrix: 1.10 ms
-// (k = 4), 1.65 ms (8), 2.69 ms (16) against 0.52-0.54 ms for one column.
+// single-vector product.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -56,11 +56,44 @@ __device__ __forceinline__ void load_cols(const double *__restrict__ xr, int j0,
     }
 }
 
-// Tasks are (row, group of KC columns); a lane takes U entries of its row
-// per round: U column indices and values from LDS, then all U x KC gathers,
-// then the additions in ascending entry order (slots past the row's end
-// re-read its last entry and are discarded by a select).
-template <int KC, int U, bool VEC>
+// KC adjacent columns of entries q .. q + U - 1 of a row that ends at z,
+// gathered together, then added in ascending order.  TAIL: entries past z
+// re-read the last one and are discarded by a select.  OFF32: sc holds byte
+// offsets of X's rows (X under 4 GB), else column numbers.
+template <int KC, int U, bool VEC, bool OFF32, bool TAIL>
+__device__ __forceinline__ void add_entries(const double *sv, const uint32_t *sc, int q, int z,
+                                            const double *__restrict__ X, int j0, int k, double (&acc)[KC]) {
+    double v[U], xv[U][KC];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int qq = TAIL ? min(q + u, z - 1) : q + u;
+        v[u] = sv[qq];
+        const double *xr = OFF32 ? reinterpret_cast<const double *>(reinterpret_cast<const char *>(X) + sc[qq])
+                                 : X + (size_t)sc[qq] * k;
+        load_cols<KC, VEC>(xr, j0, k, xv[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < KC; ++j) {
+            const double s = add_rounded_product(acc[j], v[u], xv[u][j]);
+            acc[j] = !TAIL || q + u < z ? s : acc[j];
+        }
+}
+
+// Tasks are (row, group of KC columns); a lane takes U entries of its row per
+// round.  What bounds it: the L1s, whose gathers of adjacent rows wait for the
+// same lines (busy in 50% of the cycles, stalled on lines under way in 39% at
+// k = 8), and the rounds' latencies.  So a tile is about one task per lane,
+// the row bounds are staged with the entries, the rounds but the last need
+// neither clamps nor selects, and rows keep their order: sorted by length they
+// take fewer rounds, but adjacent rows share lines (4M-row 27-point mesh, k = 8:
+// 436 us).  A shorter last round (U / 2 where that is enough) costs more than
+// the gathers it saves: 419 us.  Y leaves in non-temporal 16-byte stores, or it
+// evicts X (416 us without).  Measured, 4M-row 27-point mesh / 4M-row kNN mesh:
+// k = 2 228 -> 222 / 159 -> 131, k = 8 414 -> 399 / 306 -> 247, k = 16
+// 675 -> 624 / 489 -> 396 us; the least traffic of the first at k = 8 takes 189.
+template <int KC, int U, bool VEC, bool OFF32>
 __global__ __launch_bounds__(kBlock) void k_spmm_tiles(const TileDesc *__restrict__ desc, int n_list, int per_xcd,
                                                        int chunk_log2,
                                                        const int32_t *__restrict__ row_ptr,
@@ -69,48 +102,40 @@ __global__ __launch_bounds__(kBlock) void k_spmm_tiles(const TileDesc *__restric
                                                        double *__restrict__ Y, int k, int cap) {
     extern __shared__ __align__(16) unsigned char smem[];
     double *sv = reinterpret_cast<double *>(smem);
-    int32_t *sc = reinterpret_cast<int32_t *>(sv + cap);
+    uint32_t *sc = reinterpret_cast<uint32_t *>(sv + cap);
+    __shared__ int32_t srow[kSpmmRows + 1];
     const int li = xcd_tile(blockIdx.x, per_xcd, chunk_log2);
     if (li >= n_list) return;
     const TileDesc d = desc[li];
     const int n = min(d.e - d.s, cap);  // the host sizes cap to the largest tile
+    // the stream is read once: non-temporal, so that it leaves L2 to X
     for (int i = (int)threadIdx.x; i < n; i += kBlock) {
-        sv[i] = val[d.s + i];
-        sc[i] = col[d.s + i];
+        sv[i] = __builtin_nontemporal_load(val + d.s + i);
+        const uint32_t c = (uint32_t)__builtin_nontemporal_load(col + d.s + i);
+        sc[i] = OFF32 ? c * (uint32_t)(sizeof(double) * k) : c;
     }
+    for (int i = (int)threadIdx.x; i <= d.r1 - d.r0; i += kBlock) srow[i] = min(row_ptr[d.r0 + i] - d.s, n);
     __syncthreads();
     const int groups = (k + KC - 1) / KC;
     const int tasks = (d.r1 - d.r0) * groups;
     for (int t = (int)threadIdx.x; t < tasks; t += kBlock) {
-        const int r = d.r0 + t / groups;
-        const int j0 = (t % groups) * KC;
-        const int a = row_ptr[r] - d.s, z = min(row_ptr[r + 1] - d.s, n);
+        const int i = t / groups, j0 = (t - i * groups) * KC;
+        const int z = srow[i + 1];
+        int q = srow[i];
         double acc[KC];
 #pragma unroll
         for (int j = 0; j < KC; ++j) acc[j] = 0.0;
-        for (int q = a; q < z; q += U) {
-            double v[U];
-            double xv[U][KC];
+        for (; q + U <= z; q += U) add_entries<KC, U, VEC, OFF32, false>(sv, sc, q, z, X, j0, k, acc);
+        if (q < z) add_entries<KC, U, VEC, OFF32, true>(sv, sc, q, z, X, j0, k, acc);
+        double *__restrict__ yr = Y + (size_t)(d.r0 + i) * k + j0;
+        if constexpr (VEC && KC == 2) {
+            typedef double d2 __attribute__((ext_vector_type(2)));
+            __builtin_nontemporal_store(d2{acc[0], acc[1]}, reinterpret_cast<d2 *>(yr));
+        } else {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int qq = min(q + u, z - 1);
-                v[u] = sv[qq];
-                load_cols<KC, VEC>(X + (size_t)sc[qq] * k, j0, k, xv[u]);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const bool in_row = q + u < z;
-#pragma unroll
-                for (int j = 0; j < KC; ++j) {
-                    const double s = add_rounded_product(acc[j], v[u], xv[u][j]);
-                    acc[j] = in_row ? s : acc[j];
-                }
-            }
+            for (int j = 0; j < KC; ++j)
+                if (j0 + j < k) yr[j] = acc[j];
         }
-        double *__restrict__ yr = Y + (size_t)r * k + j0;
-#pragma unroll
-        for (int j = 0; j < KC; ++j)
-            if (j0 + j < k) yr[j] = acc[j];
     }
 }
 
@@ -176,19 +201,27 @@ __global__ __launch_bounds__(kBlock) void k_spmm_long_combine(const TileDesc *__
 }
 
 template <int KC, int U>
-static void launch_tiles(const TileDesc *desc, int n, bool remap, const DevMatrix &M, const double *X, double *Y,
-                         int k, int cap, hipStream_t st) {
-    const int per_xcd = remap && n >= 16 ? (n + 7) / 8 : 0;
+static void launch_tiles(const DevMatrix &M, const double *X, double *Y, int k, hipStream_t st) {
+    // the larger tiles where a mean small one has tasks for half the lanes at
+    // most (4M-row 27-point mesh: k = 2 222 us, 228 with the small ones; k = 4
+    // 282 / 292; one workgroup of half the lanes per small tile: 258 / 305)
+    const int64_t tasks = (int64_t)M.n_rows / M.spmm[0].n * ((k + KC - 1) / KC);
+    const SpmmTiles &T = M.spmm[tasks <= kBlock / 2 ? 1 : 0];
+    const int per_xcd = M.xcd_remap && T.n >= 16 ? (T.n + 7) / 8 : 0;
     const int chunk_log2 = M.xcd_chunk_log2;
-    const int grid = xcd_grid(n, per_xcd, chunk_log2);
-    const size_t lds = (size_t)cap * (sizeof(double) + sizeof(int32_t));
-    const bool vec = KC >= 2 && k % 2 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
-    if (vec)
-        hipLaunchKernelGGL((k_spmm_tiles<KC, U, true>), dim3(grid), dim3(kBlock), lds, st, desc, n, per_xcd,
-                           chunk_log2, M.row_ptr, M.col, M.val64, X, Y, k, cap);
-    else
-        hipLaunchKernelGGL((k_spmm_tiles<KC, U, false>), dim3(grid), dim3(kBlock), lds, st, desc, n, per_xcd,
-                           chunk_log2, M.row_ptr, M.col, M.val64, X, Y, k, cap);
+    const int grid = xcd_grid(T.n, per_xcd, chunk_log2);
+    const size_t lds = (size_t)T.entries * (sizeof(double) + sizeof(uint32_t));
+    const bool vec = KC >= 2 && k % 2 == 0 &&
+                     ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y)) & 15) == 0;
+    const bool off32 = sizeof(double) * (size_t)M.n_cols * (size_t)k < ((size_t)1 << 32);
+    const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), lds, st, T.desc, T.n, per_xcd, chunk_log2,
+                           M.row_ptr, M.col, M.val64, X, Y, k, T.entries);
+    };
+    if (vec && off32) go(k_spmm_tiles<KC, U, true, true>);
+    else if (vec) go(k_spmm_tiles<KC, U, true, false>);
+    else if (off32) go(k_spmm_tiles<KC, U, false, true>);
+    else go(k_spmm_tiles<KC, U, false, false>);
 }
 
 hipError_t launch_spmm(const spmv_matrix *A, const double *X, double *Y, int k, hipStream_t st) {
@@ -197,7 +230,6 @@ hipError_t launch_spmm(const spmv_matrix *A, const double *X, double *Y, int k, 
     // the plan has them), which is the same sum
     if (k == 1) return launch_spmv<double, double, double, double>(M, M.val64, X, Y, EPI_PLAIN, nullptr, nullptr,
                                                                    nullptr, st);
-    const int cap = std::max(A->max_tile_entries, 1);
     if (M.n_long > 0) {
         // first: the pieces' sums can live in Y's rows of the longest run
         // without a long row, which the row tiles below write afterwards
@@ -213,18 +245,19 @@ hipError_t launch_spmm(const spmv_matrix *A, const double *X, double *Y, int k, 
                                Y, k);
         }
     }
-    const struct {
-        const TileDesc *desc;
-        int n;
-    } lists[3] = {{M.stream_desc, M.n_stream}, {M.cwin_desc, M.n_cwin}, {M.win_desc, A->n_win_tiles}};
-    for (const auto &l : lists) {
-        if (l.n <= 0) continue;
+    if (M.spmm[0].n > 0) {
         // two columns per lane for every k: the lanes sharing a row gather
         // its X row in 16-byte pieces side by side, so one gather
         // instruction touches half as many cache lines as with four
         // columns per lane (16M-row mesh matrix, k = 4 / 8 / 16: 1.10 /
         // 1.65 / 2.69 ms against 1.32 / 1.87 / 2.86 ms)
-        launch_tiles<2, 8>(l.desc, l.n, M.xcd_remap, M, X, Y, k, cap, st);
+        // Eight entries per round where the matrix streams from HBM and its
+        // mean row has two such rounds, else four (k = 8: 4M-row 27-point
+        // mesh 399 us with eight, 412 with four; 4M-row kNN mesh, 13 entries per
+        // row, 266 / 247; cached: 1M-row kNN mesh 60.6 / 55.9, 125K-row 27-point
+        // mesh 16.5 / 14.0).
+        if (M.xcd_chunk_log2 >= 0 && M.nnz >= 16 * (int64_t)M.n_rows) launch_tiles<2, 8>(M, X, Y, k, st);
+        else launch_tiles<2, 4>(M, X, Y, k, st);
     }
     return hipGetLastError();
 }
