@@ -76,17 +76,21 @@ template <typename T, int KC, bool VEC> struct RowChunk {
             }
         }
     }
-    __device__ __forceinline__ static void store(T *p, const T (&o)[KC]) {
+    template <bool NT> __device__ __forceinline__ static void store(T *p, const T (&o)[KC]) {
         if constexpr (W == 1) {
 #pragma unroll
-            for (int j = 0; j < KC; ++j) p[j] = o[j];
+            for (int j = 0; j < KC; ++j) {
+                if constexpr (NT) __builtin_nontemporal_store(o[j], p + j);
+                else p[j] = o[j];
+            }
         } else {
 #pragma unroll
             for (int i = 0; i < KC; i += W) {
                 vt v;
 #pragma unroll
                 for (int w = 0; w < W; ++w) v[w] = o[i + w];
-                *reinterpret_cast<vt *>(p + i) = v;
+                if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<vt *>(p + i));
+                else *reinterpret_cast<vt *>(p + i) = v;
             }
         }
     }
@@ -199,7 +203,7 @@ __device__ __forceinline__ void bsr_triads(const BsrArgs<V, T> &g, int R0, int R
 // Pass 2, one lane per (block row, column group): the lane gathers each X
 // row once and accumulates the three scalar rows of its block row.  Same
 // per-output summation order as bsr_pairs.
-template <typename V, typename T, int K, int JL, int U, bool VEC, typename VP, typename CP>
+template <typename V, typename T, int K, int JL, int U, bool VEC, bool NT, typename VP, typename CP>
 __device__ __forceinline__ void bsr_blockrows(const BsrArgs<V, T> &g, int R0, int R1, int q0, VP vals, CP cols) {
     constexpr int KC = K / JL;
     constexpr int kRowsPerPass = kBlock / JL;
@@ -244,20 +248,20 @@ __device__ __forceinline__ void bsr_blockrows(const BsrArgs<V, T> &g, int R0, in
             }
         }
 #pragma unroll
-        for (int r = 0; r < 3; ++r) RC::store(g.Y + (size_t)(3 * br + r) * g.ldy + xoff, acc[r]);
+        for (int r = 0; r < 3; ++r) RC::template store<NT>(g.Y + (size_t)(3 * br + r) * g.ldy + xoff, acc[r]);
     }
 }
 
-template <typename V, typename T, int K, bool VEC, typename VP, typename CP>
+template <typename V, typename T, int K, bool VEC, bool NT, typename VP, typename CP>
 __device__ __forceinline__ void bsr_pass2(const BsrArgs<V, T> &g, int R0, int R1, int q0, VP vals, CP cols) {
     using Sh = BsrShape<T, K>;
     static_assert(K % Sh::JL == 0, "column groups must split K");
-    if constexpr (Sh::ROWS) bsr_blockrows<V, T, K, Sh::JL, Sh::U, VEC>(g, R0, R1, q0, vals, cols);
+    if constexpr (Sh::ROWS) bsr_blockrows<V, T, K, Sh::JL, Sh::U, VEC, NT>(g, R0, R1, q0, vals, cols);
     else if constexpr (K == 1) bsr_triads<V, T, Sh::U>(g, R0, R1, q0, vals, cols);
     else bsr_pairs<V, T, K, Sh::JL, Sh::U>(g, R0, R1, q0, vals, cols);
 }
 
-template <typename V, typename T, int K, bool VEC>
+template <typename V, typename T, int K, bool VEC, bool NT>
 __global__ __launch_bounds__(kBlock) void k_bsr3(BsrArgs<V, T> g) {
     using S = BsrStage<V>;
     __shared__ i32x4 sval_raw[S::kTrips * kBlock];
@@ -268,7 +272,7 @@ __global__ __launch_bounds__(kBlock) void k_bsr3(BsrArgs<V, T> g) {
     const int R0 = g.tiles[li], R1 = g.tiles[li + 1];
     const int q0 = g.brow_ptr[R0], q1 = g.brow_ptr[R1];
     if (q1 - q0 > kBsrBlocks) {  // one long block row: values from global memory
-        bsr_pass2<V, T, K, VEC>(g, R0, R1, q0, g.val + 9 * (size_t)q0, g.col + q0);
+        bsr_pass2<V, T, K, VEC, NT>(g, R0, R1, q0, g.val + 9 * (size_t)q0, g.col + q0);
         return;
     }
     // Pass 1.  The arrays carry 16 elements of padding past the last block,
@@ -295,7 +299,7 @@ __global__ __launch_bounds__(kBlock) void k_bsr3(BsrArgs<V, T> g) {
     __syncthreads();
     const V *sval = reinterpret_cast<const V *>(sval_raw) + vshift;
     const int32_t *scol = reinterpret_cast<const int32_t *>(scol_raw) + cshift;
-    bsr_pass2<V, T, K, VEC>(g, R0, R1, q0, sval, scol);
+    bsr_pass2<V, T, K, VEC, NT>(g, R0, R1, q0, sval, scol);
 }
 
 // One column, gathers in flight with the value stream.  Every lane issues
@@ -417,12 +421,26 @@ static void launch_k(BsrArgs<V, T> g, int grid, hipStream_t st) {
         const bool vec = ((reinterpret_cast<uintptr_t>(g.X) | reinterpret_cast<uintptr_t>(g.Y)) & 15) == 0 &&
                          g.ldx % kW == 0 && g.ldy % kW == 0 && g.off % kW == 0;
         if (vec) {
-            hipLaunchKernelGGL((k_bsr3<V, T, K, true>), dim3(grid), dim3(kBlock), 0, st, g);
+            // Y rows of 16 bytes that this launch writes whole go past L2,
+            // which leaves it to X, where the matrix streams from HBM (1.7M
+            // block rows: FP64 k = 2 268 -> 247 us, FP32 k = 4 167.4 -> 159.3;
+            // 339K block rows, in cache: 55.9 -> 56.6 and 38.1 -> 38.6, 62K:
+            // 13.2 -> 13.6 and 10.5 -> 10.8).  Wider rows and rows written by
+            // several launches were slower so (1.7M block rows: FP64 k = 4
+            // 305 -> 313 us, FP32 k = 5 / 8 / 16 332 / 232 / 693 -> 343 / 244 / 726),
+            // rows of 8 bytes and one column equal.
+            if constexpr (K * sizeof(T) == 16) {
+                if (g.ldy == K && g.chunk_log2 >= 0) {
+                    hipLaunchKernelGGL((k_bsr3<V, T, K, true, true>), dim3(grid), dim3(kBlock), 0, st, g);
+                    return;
+                }
+            }
+            hipLaunchKernelGGL((k_bsr3<V, T, K, true, false>), dim3(grid), dim3(kBlock), 0, st, g);
             return;
         }
     }
     if constexpr (K == 1) hipLaunchKernelGGL((k_bsr3_one<V, T>), dim3(grid), dim3(kBlock), 0, st, g);
-    else hipLaunchKernelGGL((k_bsr3<V, T, K, false>), dim3(grid), dim3(kBlock), 0, st, g);
+    else hipLaunchKernelGGL((k_bsr3<V, T, K, false, false>), dim3(grid), dim3(kBlock), 0, st, g);
 }
 
 template <typename V, typename T>
