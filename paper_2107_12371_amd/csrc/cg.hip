@@ -249,6 +249,16 @@ __device__ __forceinline__ bool form_alpha(CgState *st, const double *__restrict
     return true;
 }
 
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+// a b rounded on its own, never fused into the addition that takes it.
+template <typename T> __device__ __forceinline__ T product_rounded(T a, T b) {
+#pragma clang fp contract(off)
+    const T p = a * b;
+    return p;
+}
+
 // r -= alpha q and the r.r partial of each workgroup; alpha = rho / p.q from
 // the SpMV's partials (or their first-stage sums), which every workgroup sums
 // in sum_partials' order.  The first rows of a lane are loaded before the
@@ -307,7 +317,7 @@ __global__ __launch_bounds__(kBlock) void k_update_r(int n, int chunk, T *__rest
             if (i < hi) {
                 r[i] = ri;
                 d += static_cast<double>(ri) * static_cast<double>(ri);
-                if (JACOBI) dz += static_cast<double>(ri) * static_cast<double>(ds[u] * ri);
+                if (JACOBI) dz += static_cast<double>(ri) * static_cast<double>(product_rounded(ds[u], ri));
             }
         }
         i0 += kRows * kBlock;
@@ -339,7 +349,8 @@ __global__ __launch_bounds__(kBlock) void k_update_r(int n, int chunk, T *__rest
 // it or k_update_r: 4M rows in FP32, 27.6 us of updates (x and r together,
 // then p) and 9.4 us of one-workgroup reductions became 27.4 us (10.7 + 16.7).
 // JACOBI: p = z + beta p with z = D^-1 r formed again here and beta = r.z / rho;
-// z is never stored.
+// z is never stored, but rounded like a stored one before it is used, so that
+// p, r.z and a restart (k_precond_jacobi) take the same z.
 template <typename T, bool JACOBI>
 __global__ __launch_bounds__(kBlock) void k_update_xp(int n, int chunk, T *__restrict__ x, T *__restrict__ p,
                                                       const T *__restrict__ r, const T *__restrict__ dinv,
@@ -388,7 +399,7 @@ __global__ __launch_bounds__(kBlock) void k_update_xp(int n, int chunk, T *__res
             const int i = i0 + u * kBlock;
             if (i < hi) {
                 x[i] = xs[u] + a * ps[u];
-                if (more) p[i] = (JACOBI ? ds[u] * rs[u] : rs[u]) + b * ps[u];
+                if (more) p[i] = fma_t(b, ps[u], JACOBI ? product_rounded(ds[u], rs[u]) : rs[u]);
             }
         }
         i0 += kRows * kBlock;
@@ -411,9 +422,6 @@ __global__ __launch_bounds__(kBlock) void k_update_p_force(int n, T *__restrict_
     const T b = static_cast<T>(st->beta);
     for (int i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) p[i] = r[i] + b * p[i];
 }
-
-__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
-__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
 // The SpMV of a fused iteration: q = A p_new with p_new = r + beta p formed
 // for every gathered column and for the tile's own rows (the p.q partial of
