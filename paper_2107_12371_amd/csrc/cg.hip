@@ -45,6 +45,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstddef>
 #include <cstdlib>
 #include <cstring>
 #include <memory>
@@ -67,6 +68,8 @@ struct CgState {
     int32_t iter, max_iter, done, flags;
     int32_t step;  // the r update ran: the x/p update of the same iteration must run
 };
+// What the host reads of it: the fields before `step`.
+constexpr size_t kHostState = offsetof(CgState, step);
 
 // F_FRESH: the next fused product (k_spmv_pfused) takes beta from the state
 // instead of forming it from r.r partials, and records no step: set at the
@@ -1162,7 +1165,7 @@ template <typename T, typename V> struct CgCore {
     }
 
     int read_state() {
-        HIP_TRY(hipMemcpyAsync(hst, st, sizeof(CgState), hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipMemcpyAsync(hst, st, kHostState, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         return SPMV_OK;
     }

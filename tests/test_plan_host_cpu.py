@@ -1,0 +1,41 @@
+"""Host code of matrix creation and of the solvers on the CPU: the library's
+built objects linked against the mock HIP runtime (kernels never run)."""
+import importlib
+import os
+import subprocess
+
+import pytest
+
+BUILD = importlib.import_module("paper_2107_12371_amd._build")
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+MOCK = os.path.join(ROOT, "tests", "host_mock")
+HIPCC, CLANG = "/opt/rocm/bin/hipcc", "/opt/rocm/llvm/bin/clang++"
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    if not (os.path.exists(HIPCC) and os.path.exists(CLANG)):
+        pytest.skip("ROCm compilers not found")
+    objs = [os.path.join(BUILD.OBJ_DIR, s + ".o") for s in BUILD.HIP_SOURCES + BUILD.CXX_SOURCES]
+    if not all(os.path.exists(o) for o in objs):
+        BUILD.build()
+    out = tmp_path_factory.mktemp("plan_driver")
+    mock, exe = str(out / "mock_hip.o"), str(out / "plan_driver")
+    for cmd in ([HIPCC, "-O1", "-std=c++17", "-fPIC", "-c", os.path.join(MOCK, "mock_hip.cpp"), "-o", mock],
+                [CLANG, "-O1", "-std=c++17", f"-I{ROOT}/include", f"-I{BUILD.CSRC}",
+                 os.path.join(MOCK, "plan_driver.cpp"), mock, *objs, "-o", exe, "-lpthread", "-ldl"]):
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        assert r.returncode == 0, r.stdout + r.stderr
+    return exe
+
+
+def run(exe, *args):
+    r = subprocess.run([exe, *args], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout[-3000:] + r.stderr[-2000:]
+    return r.stdout
+
+
+def test_solves_reach_their_captured_iterations(driver):
+    # the mock knows the solver's state by its 96 bytes; a state of another
+    # size reads back as zeros and every solve would end before its iterations
+    run(driver, "solves_capture")
