@@ -90,16 +90,17 @@ __device__ __forceinline__ void add_entries(const double *sv, const uint32_t *sc
 // take fewer rounds, but adjacent rows share lines (4M-row 27-point mesh, k = 8:
 // 436 us).  A shorter last round (U / 2 where that is enough) costs more than
 // the gathers it saves: 419 us.  Y leaves in non-temporal 16-byte stores, or it
-// evicts X (416 us without).  Measured, 4M-row 27-point mesh / 4M-row kNN mesh:
-// k = 2 228 -> 222 / 159 -> 131, k = 8 414 -> 399 / 306 -> 247, k = 16
+// evicts X (416 us without; YNT), and so does a stream that no cache holds
+// for the next product (`stream_nt`).  Measured, 4M-row 27-point mesh / 4M-row
+// kNN mesh: k = 2 228 -> 222 / 159 -> 131, k = 8 414 -> 399 / 306 -> 247, k = 16
 // 675 -> 624 / 489 -> 396 us; the least traffic of the first at k = 8 takes 189.
-template <int KC, int U, bool VEC, bool OFF32>
+template <int KC, int U, bool VEC, bool OFF32, bool YNT>
 __global__ __launch_bounds__(kBlock) void k_spmm_tiles(const TileDesc *__restrict__ desc, int n_list, int per_xcd,
                                                        int chunk_log2,
                                                        const int32_t *__restrict__ row_ptr,
                                                        const int32_t *__restrict__ col,
                                                        const double *__restrict__ val, const double *__restrict__ X,
-                                                       double *__restrict__ Y, int k, int cap) {
+                                                       double *__restrict__ Y, int k, int cap, int stream_nt) {
     extern __shared__ __align__(16) unsigned char smem[];
     double *sv = reinterpret_cast<double *>(smem);
     uint32_t *sc = reinterpret_cast<uint32_t *>(sv + cap);
@@ -108,12 +109,15 @@ __global__ __launch_bounds__(kBlock) void k_spmm_tiles(const TileDesc *__restric
     if (li >= n_list) return;
     const TileDesc d = desc[li];
     const int n = min(d.e - d.s, cap);  // the host sizes cap to the largest tile
-    // the stream is read once: non-temporal, so that it leaves L2 to X
-    for (int i = (int)threadIdx.x; i < n; i += kBlock) {
-        sv[i] = __builtin_nontemporal_load(val + d.s + i);
-        const uint32_t c = (uint32_t)__builtin_nontemporal_load(col + d.s + i);
-        sc[i] = OFF32 ? c * (uint32_t)(sizeof(double) * k) : c;
-    }
+    const auto stage = [&](auto load) {
+        for (int i = (int)threadIdx.x; i < n; i += kBlock) {
+            sv[i] = load(val + d.s + i);
+            const uint32_t c = (uint32_t)load(col + d.s + i);
+            sc[i] = OFF32 ? c * (uint32_t)(sizeof(double) * k) : c;
+        }
+    };
+    if (stream_nt) stage([](auto *q) { return __builtin_nontemporal_load(q); });
+    else stage([](auto *q) { return *q; });
     for (int i = (int)threadIdx.x; i <= d.r1 - d.r0; i += kBlock) srow[i] = min(row_ptr[d.r0 + i] - d.s, n);
     __syncthreads();
     const int groups = (k + KC - 1) / KC;
@@ -130,7 +134,8 @@ __global__ __launch_bounds__(kBlock) void k_spmm_tiles(const TileDesc *__restric
         double *__restrict__ yr = Y + (size_t)(d.r0 + i) * k + j0;
         if constexpr (VEC && KC == 2) {
             typedef double d2 __attribute__((ext_vector_type(2)));
-            __builtin_nontemporal_store(d2{acc[0], acc[1]}, reinterpret_cast<d2 *>(yr));
+            if constexpr (YNT) __builtin_nontemporal_store(d2{acc[0], acc[1]}, reinterpret_cast<d2 *>(yr));
+            else *reinterpret_cast<d2 *>(yr) = d2{acc[0], acc[1]};
         } else {
 #pragma unroll
             for (int j = 0; j < KC; ++j)
@@ -200,6 +205,9 @@ __global__ __launch_bounds__(kBlock) void k_spmm_long_combine(const TileDesc *__
     if (lane == 0) Y[(size_t)desc[li].r0 * k + j] = tot;
 }
 
+constexpr size_t kL2Bytes = (size_t)32 << 20;  // the eight XCDs' L2s together
+static size_t matrix_bytes(const DevMatrix &M) { return (sizeof(double) + sizeof(int32_t)) * (size_t)M.nnz; }
+
 template <int KC, int U>
 static void launch_tiles(const DevMatrix &M, const double *X, double *Y, int k, hipStream_t st) {
     // the larger tiles where a mean small one has tasks for half the lanes at
@@ -213,15 +221,32 @@ static void launch_tiles(const DevMatrix &M, const double *X, double *Y, int k, 
     const size_t lds = (size_t)T.entries * (sizeof(double) + sizeof(uint32_t));
     const bool vec = KC >= 2 && k % 2 == 0 &&
                      ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y)) & 15) == 0;
-    const bool off32 = sizeof(double) * (size_t)M.n_cols * (size_t)k < ((size_t)1 << 32);
+    const size_t x_bytes = sizeof(double) * (size_t)M.n_cols * (size_t)k;
+    const bool off32 = x_bytes < ((size_t)1 << 32);
+    // The stream goes past the caches where they cannot keep it for the next
+    // product on the handle: from 272 MB of matrix and X on, a little over the
+    // 256 MB memory-side cache (one matrix, ordinary / non-temporal loads: 1M-row
+    // 27-point mesh k = 2 47 / 60 us, k = 8 (256 MB) 81 / 100, k = 12 (287 MB) 148 / 146;
+    // 2M-row kNN mesh k = 4 (226 MB) 51 / 72, k = 8 (287 MB) 116 / 106; 4M-row 27-point
+    // mesh k = 8 398 / 389), and where the matrix would fit the XCDs' L2s but for
+    // X (262K-row kNN mesh, 21 MB, k = 2 5.9 / 7.7, k = 8 13.9 / 12.0; 125K-row 27-point
+    // mesh, 25 MB, k = 4 7.9 / 8.0, k = 8 12.3 / 11.5; 512K-row kNN mesh, 40 MB, k = 8
+    // 23.2 / 29.3).
+    const size_t stream = matrix_bytes(M) + x_bytes;
+    const int stream_nt = stream > ((size_t)272 << 20) || (matrix_bytes(M) <= kL2Bytes && stream > kL2Bytes);
+    // Y past L2, but for the smallest (49K-row tet mesh k = 2 3.16 us ordinary,
+    // 3.31 non-temporal, k = 8 4.97 / 4.80; 125K-row kNN mesh k = 8 7.5 / 6.6; 1M-row
+    // 27-point mesh k = 8 104 / 81)
+    const bool y_nt = sizeof(double) * (size_t)M.n_rows * (size_t)k >= ((size_t)2 << 20);
     const auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), lds, st, T.desc, T.n, per_xcd, chunk_log2,
-                           M.row_ptr, M.col, M.val64, X, Y, k, T.entries);
+                           M.row_ptr, M.col, M.val64, X, Y, k, T.entries, stream_nt);
     };
-    if (vec && off32) go(k_spmm_tiles<KC, U, true, true>);
-    else if (vec) go(k_spmm_tiles<KC, U, true, false>);
-    else if (off32) go(k_spmm_tiles<KC, U, false, true>);
-    else go(k_spmm_tiles<KC, U, false, false>);
+    if (vec && off32 && y_nt) go(k_spmm_tiles<KC, U, true, true, true>);
+    else if (vec && off32) go(k_spmm_tiles<KC, U, true, true, false>);
+    else if (vec) go(k_spmm_tiles<KC, U, true, false, true>);
+    else if (off32) go(k_spmm_tiles<KC, U, false, true, false>);
+    else go(k_spmm_tiles<KC, U, false, false, false>);
 }
 
 hipError_t launch_spmm(const spmv_matrix *A, const double *X, double *Y, int k, hipStream_t st) {
@@ -251,12 +276,14 @@ hipError_t launch_spmm(const spmv_matrix *A, const double *X, double *Y, int k, 
         // instruction touches half as many cache lines as with four
         // columns per lane (16M-row mesh matrix, k = 4 / 8 / 16: 1.10 /
         // 1.65 / 2.69 ms against 1.32 / 1.87 / 2.86 ms)
-        // Eight entries per round where the matrix streams from HBM and its
-        // mean row has two such rounds, else four (k = 8: 4M-row 27-point
-        // mesh 399 us with eight, 412 with four; 4M-row kNN mesh, 13 entries per
-        // row, 266 / 247; cached: 1M-row kNN mesh 60.6 / 55.9, 125K-row 27-point
-        // mesh 16.5 / 14.0).
-        if (M.xcd_chunk_log2 >= 0 && M.nnz >= 16 * (int64_t)M.n_rows) launch_tiles<2, 8>(M, X, Y, k, st);
+        // Eight entries per round where the matrix is larger than the L2s, its
+        // mean row has two such rounds and columns come in pairs, else four
+        // (4M-row 27-point mesh k = 8 389 us with eight, 402 with four; 262K rows,
+        // 56 MB, k = 2 16.4 / 17.7, k = 3 25.2 / 24.4, k = 8 22.4 / 22.9; 125K rows, 26 MB,
+        // k = 2 7.0 / 5.9, k = 8 13.1 / 12.3; 4M-row kNN mesh, 7 entries per row, k = 8
+        // 254 / 236).
+        if (k % 2 == 0 && matrix_bytes(M) > kL2Bytes && M.nnz >= 16 * (int64_t)M.n_rows)
+            launch_tiles<2, 8>(M, X, Y, k, st);
         else launch_tiles<2, 4>(M, X, Y, k, st);
     }
     return hipGetLastError();
