@@ -81,6 +81,10 @@ __device__ __forceinline__ void add_entries(const double *sv, const uint32_t *sc
         }
 }
 
+// How a pair of columns of Y leaves: word by word (k odd, or Y not 16-byte
+// aligned), in one 16-byte store, or in one past L2.
+enum YStore : int { Y_WORDS, Y_PIECES, Y_PIECES_NT };
+
 // Tasks are (row, group of KC columns); a lane takes U entries of its row per
 // round.  What bounds it: the L1s, whose gathers of adjacent rows wait for the
 // same lines (busy in 50% of the cycles, stalled on lines under way in 39% at
@@ -90,11 +94,11 @@ __device__ __forceinline__ void add_entries(const double *sv, const uint32_t *sc
 // take fewer rounds, but adjacent rows share lines (4M-row 27-point mesh, k = 8:
 // 436 us).  A shorter last round (U / 2 where that is enough) costs more than
 // the gathers it saves: 419 us.  Y leaves in non-temporal 16-byte stores, or it
-// evicts X (416 us without; YNT), and so does a stream that no cache holds
+// evicts X (416 us without), and so does a stream that no cache holds
 // for the next product (`stream_nt`).  Measured, 4M-row 27-point mesh / 4M-row
 // kNN mesh: k = 2 228 -> 222 / 159 -> 131, k = 8 414 -> 399 / 306 -> 247, k = 16
 // 675 -> 624 / 489 -> 396 us; the least traffic of the first at k = 8 takes 189.
-template <int KC, int U, bool VEC, bool OFF32, bool YNT>
+template <int KC, int U, bool VEC, bool OFF32, YStore YS>
 __global__ __launch_bounds__(kBlock) void k_spmm_tiles(const TileDesc *__restrict__ desc, int n_list, int per_xcd,
                                                        int chunk_log2,
                                                        const int32_t *__restrict__ row_ptr,
@@ -132,9 +136,10 @@ __global__ __launch_bounds__(kBlock) void k_spmm_tiles(const TileDesc *__restric
         for (; q + U <= z; q += U) add_entries<KC, U, VEC, OFF32, false>(sv, sc, q, z, X, j0, k, acc);
         if (q < z) add_entries<KC, U, VEC, OFF32, true>(sv, sc, q, z, X, j0, k, acc);
         double *__restrict__ yr = Y + (size_t)(d.r0 + i) * k + j0;
-        if constexpr (VEC && KC == 2) {
+        if constexpr (YS != Y_WORDS) {
+            static_assert(KC == 2, "one 16-byte store");
             typedef double d2 __attribute__((ext_vector_type(2)));
-            if constexpr (YNT) __builtin_nontemporal_store(d2{acc[0], acc[1]}, reinterpret_cast<d2 *>(yr));
+            if constexpr (YS == Y_PIECES_NT) __builtin_nontemporal_store(d2{acc[0], acc[1]}, reinterpret_cast<d2 *>(yr));
             else *reinterpret_cast<d2 *>(yr) = d2{acc[0], acc[1]};
         } else {
 #pragma unroll
@@ -219,8 +224,10 @@ static void launch_tiles(const DevMatrix &M, const double *X, double *Y, int k, 
     const int chunk_log2 = M.xcd_chunk_log2;
     const int grid = xcd_grid(T.n, per_xcd, chunk_log2);
     const size_t lds = (size_t)T.entries * (sizeof(double) + sizeof(uint32_t));
-    const bool vec = KC >= 2 && k % 2 == 0 &&
-                     ((reinterpret_cast<uintptr_t>(X) | reinterpret_cast<uintptr_t>(Y)) & 15) == 0;
+    // X's alignment alone decides how X is gathered: with Y one word off, 4M-row
+    // 27-point mesh k = 8 takes 420 us, and 548 with X gathered word by word
+    const bool vec = KC >= 2 && k % 2 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+    const bool pieces = vec && (reinterpret_cast<uintptr_t>(Y) & 15) == 0;
     const size_t x_bytes = sizeof(double) * (size_t)M.n_cols * (size_t)k;
     const bool off32 = x_bytes < ((size_t)1 << 32);
     // The stream goes past the caches where they cannot keep it for the next
@@ -242,11 +249,13 @@ static void launch_tiles(const DevMatrix &M, const double *X, double *Y, int k, 
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), lds, st, T.desc, T.n, per_xcd, chunk_log2,
                            M.row_ptr, M.col, M.val64, X, Y, k, T.entries, stream_nt);
     };
-    if (vec && off32 && y_nt) go(k_spmm_tiles<KC, U, true, true, true>);
-    else if (vec && off32) go(k_spmm_tiles<KC, U, true, true, false>);
-    else if (vec) go(k_spmm_tiles<KC, U, true, false, true>);
-    else if (off32) go(k_spmm_tiles<KC, U, false, true, false>);
-    else go(k_spmm_tiles<KC, U, false, false, false>);
+    if (pieces && off32 && y_nt) go(k_spmm_tiles<KC, U, true, true, Y_PIECES_NT>);
+    else if (pieces && off32) go(k_spmm_tiles<KC, U, true, true, Y_PIECES>);
+    else if (pieces) go(k_spmm_tiles<KC, U, true, false, Y_PIECES_NT>);
+    else if (vec && off32) go(k_spmm_tiles<KC, U, true, true, Y_WORDS>);
+    else if (vec) go(k_spmm_tiles<KC, U, true, false, Y_WORDS>);
+    else if (off32) go(k_spmm_tiles<KC, U, false, true, Y_WORDS>);
+    else go(k_spmm_tiles<KC, U, false, false, Y_WORDS>);
 }
 
 hipError_t launch_spmm(const spmv_matrix *A, const double *X, double *Y, int k, hipStream_t st) {
