@@ -22,7 +22,6 @@ template <typename V, typename T> struct JagArgs {
     double *part;          // EPI_DOT / EPI_RESID: one partial per tile
     const int *done;       // optional: non-zero makes the launch a no-op (CG)
     int32_t n_tiles, per_xcd, chunk_log2, stride, n_cols;
-    int32_t x_aligned;     // x is 16-byte aligned
 };
 
 // y = A x (or its epilogues) over the handle's jagged tiles; partial t of

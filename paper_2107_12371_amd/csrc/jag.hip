@@ -62,6 +62,17 @@ __device__ __forceinline__ int scalar(int v) {
     return v;
 }
 
+// 16 or 4 bytes of every lane from its own address straight to LDS, where the
+// lanes' pieces follow each other from dst (the same for the wavefront) on.
+typedef const __attribute__((address_space(1))) void GlobalPtr;
+typedef __attribute__((address_space(3))) void LdsPtr;
+__device__ __forceinline__ void to_lds16(const void *src, void *dst) {
+    __builtin_amdgcn_global_load_lds((GlobalPtr *)src, (LdsPtr *)dst, 16, 0, 0);
+}
+__device__ __forceinline__ void to_lds4(const void *src, void *dst) {
+    __builtin_amdgcn_global_load_lds((GlobalPtr *)src, (LdsPtr *)dst, 4, 0, 0);
+}
+
 // Position M (0..7) of the 8 packed in three words.
 template <int M> __device__ __forceinline__ unsigned pos12(uint32_t w0, uint32_t w1, uint32_t w2) {
     if constexpr (M < 5) return (unsigned)(((uint64_t)w0 | ((uint64_t)w1 << 32)) >> (12 * M)) & 0xfffu;
@@ -69,8 +80,13 @@ template <int M> __device__ __forceinline__ unsigned pos12(uint32_t w0, uint32_t
 }
 
 // G: groups of 4 entries the longest row of the handle's tiles has (the
-// registers a lane holds its row in).
-template <typename V, typename T, int G, int EPI>
+// registers a lane holds its row in).  X16: x is 16-byte aligned; any other x
+// has a kernel of its own, which the aligned one does not pay for (as a branch
+// it did: FP32, 2M-row kNN mesh, 16.8 -> 17.7 us).  x one word off, staged word by
+// word through registers -> in steps of 4 bytes straight to LDS: 4M-row 27-point
+// mesh FP32 / BF16 / binary64 with FP32 values 101 / 103 / 131 -> 79 / 67 / 97 us (the
+// row tiles 82 / 74 / 99).
+template <typename V, typename T, int G, int EPI, bool X16>
 __global__ __launch_bounds__(kJagRows) void k_jag(JagArgs<V, T> g) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double sh[kJagRows / kWave];
@@ -96,7 +112,7 @@ __global__ __launch_bounds__(kJagRows) void k_jag(JagArgs<V, T> g) {
     const int32_t *__restrict__ h = g.hdr + ((size_t)li * kWaves + wave) * kJagHdr;
     int vb = h[0], pb = h[1];
     const int ns = h[2], r0 = h[3], nr = h[4];
-    const bool whole = h[5] == 0 && g.x_aligned != 0;
+    const bool whole = h[5] == 0;
     int32_t cnt[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) cnt[i] = h[8 + i];
@@ -107,16 +123,25 @@ __global__ __launch_bounds__(kJagRows) void k_jag(JagArgs<V, T> g) {
         for (int i = 0; i < kRegs * kPpr; ++i) {
             const int base = (i * kWaves + wave) * kSpp;
             if (base < ns) {
-                const int s = __shfl(sr[i / kPpr], (i % kPpr) * kSpp + lane / kLanes, kWave);
-                const T *src = g.x + (size_t)s * kJagSector + (lane % kLanes) * kPiece;
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
-                                                 (__attribute__((address_space(3))) void *)(win + base * kJagSector),
-                                                 16, 0, 0);
+                if constexpr (X16) {
+                    const int s = __shfl(sr[i / kPpr], (i % kPpr) * kSpp + lane / kLanes, kWave);
+                    const T *src = g.x + (size_t)s * kJagSector + (lane % kLanes) * kPiece;
+                    to_lds16(src, win + base * kJagSector);
+                } else {  // the same pass in four steps of 4 bytes per lane
+                    constexpr int kBytes = kJagSector * (int)sizeof(T), kStep = 4 * kWave / kBytes;  // sectors a step
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const int at = (i % kPpr) * kSpp + j * kStep + lane / (kBytes / 4);
+                        const int s = __shfl(sr[i / kPpr], at, kWave);
+                        to_lds4(reinterpret_cast<const char *>(g.x) + (size_t)s * kBytes + lane % (kBytes / 4) * 4,
+                                win + (base + j * kStep) * kJagSector);
+                    }
+                }
             }
         }
     } else {
-        // x not 16-byte aligned, or a sector that reaches past x's end: one
-        // word at a time, columns clamped into x
+        // a sector that reaches past x's end: one word at a time, columns
+        // clamped into x
         for (int w = tid; w < ns * kJagSector; w += kJagRows)
             win[w] = g.x[min(sect[w / kJagSector] * kJagSector + w % kJagSector, g.n_cols - 1)];
     }
@@ -294,10 +319,14 @@ __global__ __launch_bounds__(kJagRows) void k_jag_fill_val(const int32_t *__rest
 
 template <typename V, typename T, int G>
 static void launch_groups(const JagArgs<V, T> &a, int epi, int grid, size_t lds, hipStream_t st) {
+    const bool x16 = (reinterpret_cast<uintptr_t>(a.x) & 15) == 0;
+    const auto go = [&](auto aligned, auto other) {
+        hipLaunchKernelGGL(x16 ? aligned : other, dim3(grid), dim3(kJagRows), lds, st, a);
+    };
     switch (epi) {
-        case EPI_DOT: hipLaunchKernelGGL((k_jag<V, T, G, EPI_DOT>), dim3(grid), dim3(kJagRows), lds, st, a); break;
-        case EPI_RESID: hipLaunchKernelGGL((k_jag<V, T, G, EPI_RESID>), dim3(grid), dim3(kJagRows), lds, st, a); break;
-        default: hipLaunchKernelGGL((k_jag<V, T, G, EPI_PLAIN>), dim3(grid), dim3(kJagRows), lds, st, a); break;
+        case EPI_DOT: go(k_jag<V, T, G, EPI_DOT, true>, k_jag<V, T, G, EPI_DOT, false>); break;
+        case EPI_RESID: go(k_jag<V, T, G, EPI_RESID, true>, k_jag<V, T, G, EPI_RESID, false>); break;
+        default: go(k_jag<V, T, G, EPI_PLAIN, true>, k_jag<V, T, G, EPI_PLAIN, false>); break;
     }
 }
 
@@ -319,7 +348,6 @@ void launch_jag(const DevMatrix &M, const V *val, const SpmvArgs<V, T, T> &g, in
     a.chunk_log2 = M.xcd_chunk_log2;
     a.stride = M.jag_stride;
     a.n_cols = M.n_cols;
-    a.x_aligned = (reinterpret_cast<uintptr_t>(g.x) & 15) == 0;
     const int grid = xcd_grid(M.n_jag, a.per_xcd, a.chunk_log2);
     // LDS for the handle's widest window in whole staging passes (at most
     // 256 words each), and at least one word per row for the way back to
