@@ -10,8 +10,8 @@
 // that one of them brings into the XCD's L2 serves the others before it is
 // dropped.  Entries carry their place in the tile (16 bits); after a barrier
 // the products are summed row by row in CSR order, each rounded before it is
-// added: the row tiles' sums, same bits.  The number of tiles is a multiple
-// of the CUs, so that no round of workgroups is nearly empty.
+// added: the row tiles' sums, same bits.  The tiles fill whole rounds of one
+// workgroup per CU, so that no round is nearly empty.
 // Measured, row tiles -> sweep tiles, FP64, random order, three matrices in
 // turn: kNN mesh of 1M rows 71.3 -> 54.7 us, 2M rows 181 -> 112 us, 8M rows
 // 907 -> 696 us; 27-point mesh of 1M rows 173 -> 120 us, 4M rows 1,106 -> 723
@@ -89,6 +89,15 @@ __global__ __launch_bounds__(kSweepLanes) void k_sweep(const TileDesc *__restric
         const int a = row_ptr[r] - d.s, z = row_ptr[r + 1] - d.s;
         T sum = T(0);
         int k = a;
+        // one lane's chain of LDS reads and adds: a row of 2,000 entries takes
+        // 21 us read by fours and 9.5 by sixteens, with the CU waiting for it
+        for (; k + 16 <= z; k += 16) {
+            T q[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) q[u] = prod[k + u];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) sum = add_each(sum, q[u]);
+        }
         for (; k + 4 <= z; k += 4) {
             T q[4];
 #pragma unroll
