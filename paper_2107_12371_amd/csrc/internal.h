@@ -133,6 +133,7 @@ bool build_jag_plan(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *
 // long row among them), worked in order of column.  For scattered columns and
 // entries for a round of workgroups that nearly fill their CUs.
 constexpr int64_t kSweepMinNnz = int64_t(1) << 22;
+constexpr int32_t kSweepTarget = 19500;  // most entries aimed at: a tile ends with a row, at most at kSweepTile
 
 struct SweepPlan {
     int32_t width = 0;            // entries of the largest tile

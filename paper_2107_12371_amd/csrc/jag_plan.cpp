@@ -191,28 +191,69 @@ bool build_sweep_plan(int32_t n_rows, int32_t n_cols, const int32_t *row_ptr, co
     S = SweepPlan{};
     if (lines_per_entry(n_rows, row_ptr, col_idx, long_len) < 0.75) return false;
     const auto len_of = [row_ptr](int32_t r) { return row_ptr[r + 1] - row_ptr[r]; };
+    // entries of the runs of rows between long rows: a tile ends with its run
+    std::vector<int64_t> run;
     int64_t entries = 0;
-    for (int32_t r = 0; r < n_rows; ++r)
-        if (len_of(r) <= long_len) entries += len_of(r);
+    for (int32_t r = 0, last = -2; r < n_rows; ++r) {
+        if (len_of(r) > long_len) continue;
+        if (r != last + 1) run.push_back(0);
+        run.back() += len_of(r);
+        entries += len_of(r);
+        last = r;
+    }
     if (entries < kSweepMinNnz) return false;
-    // whole rounds of one workgroup per CU, each tile some rows short of full
-    const int64_t rounds = (entries + (int64_t)n_cus * 19500 - 1) / ((int64_t)n_cus * 19500);
-    const int32_t target = (int32_t)((entries + rounds * n_cus - 1) / (rounds * n_cus));
+    // Tiles of at least `target` entries, as many as whole rounds of one
+    // workgroup per CU hold: the smallest such target for each number of
+    // rounds, and of those the quickest.  A workgroup takes as long as for its
+    // entries and some 3,600 more (2M-row kNN mesh, tiles of 20,480 / 16,384 /
+    // 8,192 / 4,096 entries: 117 / 122 / 143 / 175 us).
+    const auto cost = [n_cus](int64_t rounds, int64_t target) { return rounds * n_cus * (target + 3600); };
+    const int64_t least = (entries + (int64_t)n_cus * kSweepTarget - 1) / ((int64_t)n_cus * kSweepTarget);
+    constexpr int kMoreRounds = 3;
+    if ((int64_t)run.size() > (least + kMoreRounds) * n_cus) return false;
+    int32_t target = 0;
+    int64_t best = INT64_MAX;
+    for (int64_t rounds = least; rounds <= least + kMoreRounds; ++rounds) {
+        int32_t lo = 1, hi = kSweepTarget + 1;  // the first that fits lies in [lo, hi]; hi: none
+        while (lo < hi) {
+            const int32_t mid = (lo + hi) / 2;
+            int64_t tiles = 0;
+            for (const int64_t e : run) tiles += std::max<int64_t>((e + mid - 1) / mid, 1);
+            if (tiles <= rounds * n_cus) hi = mid;
+            else lo = mid + 1;
+        }
+        if (lo <= kSweepTarget && cost(rounds, lo) < best) {
+            target = lo;
+            best = cost(rounds, lo);
+        }
+    }
+    if (!target) return false;
+    int64_t chains = 0;  // the tiles' longest rows
     for (int32_t r = 0; r < n_rows;) {
         if (len_of(r) > long_len) {
             ++r;
             continue;
         }
         const int32_t s = row_ptr[r];
-        int32_t r1 = r;
-        while (r1 < n_rows && len_of(r1) <= long_len && row_ptr[r1] - s < target && row_ptr[r1 + 1] - s <= kSweepTile)
-            ++r1;
+        int32_t r1 = r, longest = 0;
+        while (r1 < n_rows && len_of(r1) <= long_len && (row_ptr[r1] - s < target || len_of(r1) == 0) &&
+               row_ptr[r1 + 1] - s <= kSweepTile)
+            longest = std::max(longest, len_of(r1++));
+        chains += longest;
         S.bound.push_back(r);
         S.bound.push_back(r1);
         S.width = std::max(S.width, row_ptr[r1] - s);
         r = r1;
     }
     const int32_t nt = (int32_t)(S.bound.size() / 2);
+    // Row tiles take as long as 1.5 to 1.9 times the entries in the same unit, a
+    // tile's longest row (one lane's chain) up to 4 per entry: where many long
+    // rows leave small tiles, or many tiles hold such a row, row tiles are the
+    // quicker (kNN mesh, row / sweep tiles: 2M rows with 64 / 512 rows of 2,100
+    // entries for long rows 190 / 127 and 199 / 208 us; 2M rows, 2,000 rows of 1,000
+    // entries 222 / 189; 804K rows, 200 rows of 2,000 entries 73 / 78).
+    const int64_t rounds = (nt + n_cus - 1) / n_cus;
+    if (2 * (cost(rounds, target) + 4 * chains) > 3 * entries) return false;
     S.n = (size_t)row_ptr[n_rows];
     S.place.reset(new uint16_t[S.n]);  // the long rows' parts stay unset and unread
     // order of column, to 1/2048 of the columns' range (a stable counting

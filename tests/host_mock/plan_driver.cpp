@@ -1,11 +1,14 @@
 // Host code of matrix creation and of the solvers against the mock HIP
 // runtime; the first argument names the check.  Prints what was found and
 // exits 0 when the check holds.
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <utility>
 #include <vector>
 
+#include "internal.h"
 #include "spmv.h"
 
 extern "C" const char *mock_launch_log(void);
@@ -64,11 +67,66 @@ void solves_capture() {
     spmv_destroy(M);
 }
 
+// Sweep tiles beside long rows: whole rounds of workgroups while the tiles
+// stay large, row tiles where they do not.
+void sweep_rounds() {
+    constexpr int kCus = 256, kLong = 1021, kRows = 1'000'000, kPerRow = 7;
+    uint32_t lcg = 1;
+    std::vector<int32_t> row_ptr, col;
+    for (const auto &[n_long, taken] : {std::pair{0, true}, {1, true}, {8, true}, {64, true}, {512, false}, {8192, false}}) {
+        row_ptr.assign(1, 0);
+        col.clear();
+        for (int r = 0, next = 0; r < kRows; ++r) {
+            int len = kPerRow;
+            if (next < n_long && r == (int)((int64_t)(next + 1) * kRows / (n_long + 1))) {
+                len = kLong + 1;
+                ++next;
+            }
+            for (int k = 0; k < len; ++k) {
+                lcg = lcg * 1664525u + 1013904223u;
+                col.push_back((int32_t)((uint64_t)lcg * kRows >> 32));
+            }
+            row_ptr.push_back((int32_t)col.size());
+        }
+        spmvlib::SweepPlan S;
+        const bool built = spmvlib::build_sweep_plan(kRows, kRows, row_ptr.data(), col.data(), kLong, kCus, S);
+        const std::string what = std::to_string(n_long) + " long rows";
+        check(built == taken, (what + ": taken or left as expected").c_str());
+        if (!built) continue;
+        const int tiles = (int)(S.bound.size() / 2);
+        std::printf("  %d tiles, width %d\n", tiles, S.width);
+        check(tiles <= 2 * kCus, (what + ": two rounds of workgroups").c_str());
+        check(S.width <= spmvlib::kSweepTile, (what + ": tiles fit the LDS").c_str());
+        // every row that is not long in one tile, in order
+        int64_t rows = 0;
+        for (int t = 0; t < tiles; ++t) rows += S.bound[2 * t + 1] - S.bound[2 * t];
+        check(rows == kRows - n_long, (what + ": every other row in a tile").c_str());
+    }
+    // a run that ends in empty rows, and runs of empty rows alone
+    std::vector<int> lens(800'000, 6);
+    std::fill(lens.end() - 1000, lens.end(), 0);
+    for (int r : {1000, 1002, 1004}) lens[r] = 2000;
+    lens[1001] = lens[1003] = 0;
+    row_ptr.assign(1, 0);
+    col.clear();
+    for (int len : lens) {
+        for (int k = 0; k < len; ++k) {
+            lcg = lcg * 1664525u + 1013904223u;
+            col.push_back((int32_t)((uint64_t)lcg * kRows >> 32));
+        }
+        row_ptr.push_back((int32_t)col.size());
+    }
+    spmvlib::SweepPlan S;
+    check(spmvlib::build_sweep_plan((int)lens.size(), kRows, row_ptr.data(), col.data(), kLong, kCus, S), "empty rows");
+    check(S.bound.size() / 2 <= kCus, "empty rows: one round of workgroups");
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "solves_capture") solves_capture();
+    else if (what == "sweep_rounds") sweep_rounds();
     else ++failures;
     return failures ? 1 : 0;
 }

@@ -39,3 +39,9 @@ def test_solves_reach_their_captured_iterations(driver):
     # the mock knows the solver's state by its 96 bytes; a state of another
     # size reads back as zeros and every solve would end before its iterations
     run(driver, "solves_capture")
+
+
+def test_sweep_tiles_beside_long_rows(driver):
+    # a long row ends a tile: the tiles must still fill whole rounds of one
+    # workgroup per CU, or the matrix keeps its row tiles
+    run(driver, "sweep_rounds")
