@@ -1,7 +1,11 @@
 // Host code of matrix creation and of the solvers against the mock HIP
 // runtime; the first argument names the check.  Prints what was found and
 // exits 0 when the check holds.
+#include <sys/resource.h>
+
 #include <algorithm>
+#include <climits>
+#include <cstdint>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -121,12 +125,39 @@ void sweep_rounds() {
     check(S.bound.size() / 2 <= kCus, "empty rows: one round of workgroups");
 }
 
+// 4,200 tiles' worth of a banded matrix, its columns `shift` to the right.
+Csr banded(int32_t n, int32_t n_cols, int32_t shift) {
+    Csr A;
+    A.n_cols = n_cols;
+    for (int32_t i = 0; i < n; ++i) {
+        for (int32_t d = 0; d < 18; ++d) A.col.push_back(shift + std::min(i + d, n - 1));
+        A.end_row();
+    }
+    return A;
+}
+
+// The plan's memory follows the matrix's entries, not its number of columns.
+void wide_matrix() {
+    const int32_t n = 70'000, n_cols = INT32_MAX;
+    const Csr A = banded(n, n_cols, n_cols - n);
+    spmv_matrix *M = nullptr;
+    spmv_info info{};
+    check(A.create(nullptr, 0, &M) == SPMV_OK && spmv_get_info(M, &info) == SPMV_OK, "create");
+    check(info.device_bytes > 20 * info.nnz, "the layout of its products is there");
+    rusage u{};
+    getrusage(RUSAGE_SELF, &u);
+    std::printf("  peak %ld MB\n", u.ru_maxrss / 1024);
+    check(u.ru_maxrss < 1024 * 1024, "peak host memory below 1 GB");
+    spmv_destroy(M);
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "solves_capture") solves_capture();
     else if (what == "sweep_rounds") sweep_rounds();
+    else if (what == "wide_matrix") wide_matrix();
     else ++failures;
     return failures ? 1 : 0;
 }

@@ -45,3 +45,8 @@ def test_sweep_tiles_beside_long_rows(driver):
     # a long row ends a tile: the tiles must still fill whole rounds of one
     # workgroup per CU, or the matrix keeps its row tiles
     run(driver, "sweep_rounds")
+
+
+def test_plan_memory_of_a_wide_matrix(driver):
+    # 2^31 - 1 columns, 1.3M entries
+    run(driver, "wide_matrix")
