@@ -330,7 +330,7 @@ static int upload_sweep(Uploader &U, DevMatrix &M, const SweepPlan &S, const int
         rc = U.reserve(&M.sweep32, n_pad, n);
         if (!rc) launch_sweep_fill_val<float>(M, M.val32, M.sweep32, U.s);
     }
-    if (!rc && M.val16 && sweep_pays<float>(M)) {
+    if (!rc && M.val16 && sweep_pays<float>(M.n_cols)) {
         rc = U.reserve(&M.sweep16, n_pad, n);
         if (!rc) launch_sweep_fill_val<uint16_t>(M, M.val16, M.sweep16, U.s);
     }
@@ -346,26 +346,40 @@ static int upload_sweep(Uploader &U, DevMatrix &M, const SweepPlan &S, const int
 // binary64 ones of plans without compact windows (k_cwin reads as many bytes
 // and is as fast there: 133 us either way on the 4M-row 27-point mesh, where
 // FP32 takes 77.7 against 81.0 and BF16 68.0 against 73.2 us); sweep tiles for
-// plans without windows whose columns are scattered.  Without memory for a
-// layout the handle keeps its row tiles.
-static void add_layouts(Uploader &U, DevMatrix &M, const int32_t *row_ptr, const int32_t *col_idx,
-                        const spmv_params *p, const std::vector<TileDesc> &long_desc) {
+// plans without windows whose columns are scattered.
+struct Layouts {
+    JagPlan jag;
+    SweepPlan sweep;
+    bool plain = false;  // binary64 products too
+    bool has_jag = false, has_sweep = false;
+};
+
+// Host work alone, so that it is done before the capture gate is taken.
+static void plan_layouts(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *row_ptr, const int32_t *col_idx,
+                         const Plan &P, uint32_t flags, const spmv_params *p, Layouts &L) {
     if (p && (p->tile_nnz || p->tile_rows || p->window_mode != SPMV_WINDOW_AUTO || p->window_gap || p->kernel)) return;
-    const bool plain = M.n_cwin == 0;
-    if (M.nnz < kJagMinNnz || !(plain || M.val32 || M.val16)) return;
+    L.plain = P.cwin_list.empty();
+    if (nnz < kJagMinNnz || !(L.plain || (flags & (SPMV_VALUES_FP32 | SPMV_VALUES_BF16)))) return;
+    try {
+        const int cap = P.tile_nnz - 3;
+        L.has_jag = build_jag_plan(n_rows, n_cols, nnz, row_ptr, col_idx, cap, L.jag);
+        if (!L.has_jag && L.plain && sweep_pays<double>(n_cols))
+            L.has_sweep = build_sweep_plan(n_rows, n_cols, row_ptr, col_idx, cap, device_cus(), L.sweep);
+    } catch (const std::exception &) {
+        L.has_jag = L.has_sweep = false;
+    }
+}
+
+// Without memory for the layout the handle keeps its row tiles.
+static void add_layouts(Uploader &U, DevMatrix &M, const int32_t *row_ptr, const Layouts &L,
+                        const std::vector<TileDesc> &long_desc) {
+    if (!L.has_jag && !L.has_sweep) return;
     const DevMatrix before = M;
     const size_t keep = U.A->allocs.size();
     const int64_t bytes = U.A->bytes;
     int rc = SPMV_OK;
     try {
-        JagPlan J;
-        SweepPlan S;
-        const int cap = M.tile_nnz - 3;
-        if (build_jag_plan(M.n_rows, M.n_cols, M.nnz, row_ptr, col_idx, cap, J))
-            rc = upload_jag(U, M, J, row_ptr, long_desc, plain);
-        else if (plain && sweep_pays<double>(M) &&
-                 build_sweep_plan(M.n_rows, M.n_cols, row_ptr, col_idx, cap, device_cus(), S))
-            rc = upload_sweep(U, M, S, row_ptr);
+        rc = L.has_jag ? upload_jag(U, M, L.jag, row_ptr, long_desc, L.plain) : upload_sweep(U, M, L.sweep, row_ptr);
     } catch (const std::exception &) {
         rc = SPMV_ENOMEM;
     }
@@ -524,6 +538,8 @@ static int create_csr(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t
     Plan P;
     int rc = build_plan(n_rows, n_cols, nnz, row_ptr, col_idx, params, P);
     if (rc) return rc;
+    Layouts L;
+    plan_layouts(n_rows, n_cols, nnz, row_ptr, col_idx, P, flags, params, L);
 
     auto *A = new (std::nothrow) spmv_matrix();
     if (!A) return fail(SPMV_ENOMEM, "host allocation failed");
@@ -602,7 +618,7 @@ static int create_csr(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t
             A->max_tile_entries = std::max(A->max_tile_entries,
                                            row_ptr[P.seg_bound[sg + 1]] - row_ptr[P.seg_bound[sg]]);
     if (!rc) rc = upload_spmm(U, M, P, row_ptr);
-    if (!rc) add_layouts(U, M, row_ptr, col_idx, params, d);
+    if (!rc) add_layouts(U, M, row_ptr, L, d);
     if (!rc) prepare_launch_queries();
     if (!rc && M.n_blk) {
         hipError_t e2 = prepare_window_kernels();

@@ -627,7 +627,7 @@ static hipError_t launch_nt(const DevMatrix &M, SpmvArgs<V, X, Y> g, hipStream_t
     launch_long<V, X, Y, A, EPI>(M, g, M.long_desc, st);
     if constexpr (EPI == EPI_PLAIN) {
         // scattered orderings (the solvers' epilogues keep the row tiles)
-        const V *sv = sweep_pays<X>(M) ? sweep_values<V>(M) : nullptr;
+        const V *sv = sweep_pays<X>(M.n_cols) ? sweep_values<V>(M) : nullptr;
         if (sv) {
             launch_sweep<V, X>(M, sv, g.x, g.y, g.done, st);
             return hipGetLastError();

@@ -33,8 +33,6 @@ template <> inline const uint16_t *sweep_values<uint16_t>(const DevMatrix &M) { 
 // 26.7 us, 6.9 MB 57.6 -> 49.7, 8 MB 72.4 -> 58.3; FP32 x of 4 MB 39.8 -> 47.1,
 // 8 MB 119.6 -> 93.7).
 constexpr int64_t kSweepMinXBytes = int64_t(6) << 20;
-template <typename X> inline bool sweep_pays(const DevMatrix &M) {
-    return (int64_t)sizeof(X) * M.n_cols >= kSweepMinXBytes;
-}
+template <typename X> inline bool sweep_pays(int32_t n_cols) { return (int64_t)sizeof(X) * n_cols >= kSweepMinXBytes; }
 
 }  // namespace spmvlib

@@ -1,14 +1,18 @@
 // Host code of matrix creation and of the solvers against the mock HIP
 // runtime; the first argument names the check.  Prints what was found and
 // exits 0 when the check holds.
+#include <dlfcn.h>
+#include <pthread.h>
 #include <sys/resource.h>
 
 #include <algorithm>
+#include <atomic>
 #include <climits>
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <thread>
 #include <utility>
 #include <vector>
 
@@ -16,6 +20,35 @@
 #include "spmv.h"
 
 extern "C" const char *mock_launch_log(void);
+
+// Threads started while the library's capture gate was held.
+static std::atomic<int> started{0}, under_gate{0};
+
+struct Start {
+    void *(*f)(void *);
+    void *arg;
+    std::atomic<bool> looked{false};
+};
+
+static void *look_at_gate(void *p) {
+    Start *s = static_cast<Start *>(p);
+    void *(*f)(void *) = s->f, *arg = s->arg;
+    if (spmvlib::capture_gate().try_lock()) spmvlib::capture_gate().unlock();
+    else ++under_gate;
+    s->looked = true;
+    return f(arg);
+}
+
+// Every thread of the process starts here; the caller waits until it has looked.
+extern "C" int pthread_create(pthread_t *t, const pthread_attr_t *a, void *(*f)(void *), void *arg) {
+    static const auto real = reinterpret_cast<int (*)(pthread_t *, const pthread_attr_t *, void *(*)(void *), void *)>(
+        dlsym(RTLD_NEXT, "pthread_create"));
+    Start s{f, arg};
+    const int rc = real(t, a, look_at_gate, &s);
+    ++started;
+    while (rc == 0 && !s.looked) std::this_thread::yield();
+    return rc;
+}
 
 namespace {
 
@@ -151,6 +184,18 @@ void wide_matrix() {
     spmv_destroy(M);
 }
 
+// A layout's host work keeps no solve of another thread from its capture.
+void plans_without_gate() {
+    const Csr A = banded(120'000, 120'000, 0);
+    spmv_matrix *M = nullptr;
+    spmv_info info{};
+    check(A.create(nullptr, 0, &M) == SPMV_OK && spmv_get_info(M, &info) == SPMV_OK, "create");
+    check(info.device_bytes > 20 * info.nnz, "the layout of its products is there");
+    std::printf("  %d threads started, %d while the gate was held\n", started.load(), under_gate.load());
+    check(started > 0 && under_gate == 0, "no thread started while the gate was held");
+    spmv_destroy(M);
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -158,6 +203,7 @@ int main(int argc, char **argv) {
     if (what == "solves_capture") solves_capture();
     else if (what == "sweep_rounds") sweep_rounds();
     else if (what == "wide_matrix") wide_matrix();
+    else if (what == "plans_without_gate") plans_without_gate();
     else ++failures;
     return failures ? 1 : 0;
 }

@@ -50,3 +50,8 @@ def test_sweep_tiles_beside_long_rows(driver):
 def test_plan_memory_of_a_wide_matrix(driver):
     # 2^31 - 1 columns, 1.3M entries
     run(driver, "wide_matrix")
+
+
+def test_layouts_are_planned_outside_the_capture_gate(driver):
+    # the gate also holds back every graph capture of the process
+    run(driver, "plans_without_gate")
