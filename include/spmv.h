@@ -73,8 +73,9 @@ typedef struct spmv_matrix spmv_matrix;
                                    arrays of the current device, holding n_rows + 1, nnz
                                    and nnz elements (9 nnz_blocks values for block CSR);
                                    they are copied to the host for the plan, then
-                                   uploaded as host arrays are.  A pointer the runtime
-                                   does not know as device memory is SPMV_EINVAL */
+                                   uploaded as host arrays are (the values of a CSR-
+                                   format handle stay on the device).  A pointer the
+                                   runtime does not know as device memory is SPMV_EINVAL */
 
 /* x-window policy.  The GPU counterparts of the paper's vector cache
  * (Sec. 5.1): x words a tile needs are staged in LDS with contiguous loads
@@ -184,6 +185,17 @@ typedef struct spmv_info {
  *                   SPMV_DEVICE_PTRS
  *   params          NULL for defaults
  *   out             receives the new handle (NULL on failure)
+ * Device memory (spmv_info.device_bytes): 12 bytes per entry, 4 and 2 more
+ * for FP32 and BF16 values, and the vectors of the plan.  A CSR-format handle
+ * of 2^20 entries and more also keeps its entries in a second order where its
+ * products are faster in it: about 1.6 bytes per entry and a copy of the
+ * values (binary64 ones unless the plan has windows), or, for scattered
+ * columns, 6 bytes per entry and a copy of the values.  It does so only while
+ * half of the device's memory stays free, and not at all when tile_nnz,
+ * tile_rows, window_mode, window_gap or kernel is set (window_gap = 64, its
+ * default, changes nothing else).  Products have the same bits either way;
+ * cg_solve sums its dot products by the tiles of the order in use, so its
+ * iterates may differ in their last bits.
  * The caller keeps ownership of its arrays.  The device is the current HIP
  * device.  Errors: SPMV_EINVAL (malformed input), SPMV_ENOMEM, SPMV_EDEVICE.
  */

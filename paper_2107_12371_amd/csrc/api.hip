@@ -16,6 +16,9 @@
 #include "spmm.h"
 #include "sweep.h"
 
+// Weak: a host-only stand-in for the runtime need not have it.
+extern "C" hipError_t hipMemGetInfo(size_t *free, size_t *total) __attribute__((weak));
+
 namespace spmvlib {
 
 namespace {
@@ -370,10 +373,22 @@ static void plan_layouts(int32_t n_rows, int32_t n_cols, int64_t nnz, const int3
     }
 }
 
-// Without memory for the layout the handle keeps its row tiles.
+// Device bytes of a layout.
+static size_t layout_bytes(const DevMatrix &M, const Layouts &L) {
+    const size_t narrow = (M.val32 ? sizeof(float) : 0) + (M.val16 ? sizeof(uint16_t) : 0);
+    if (L.has_sweep) return L.sweep.n * (sizeof(uint16_t) + sizeof(int32_t) + sizeof(double) + narrow);
+    return 4 * (L.jag.hdr.size() + L.jag.sect.size() + (size_t)L.jag.n_words) + 2 * L.jag.slot.size() +
+           (size_t)L.jag.n_entries * ((L.plain ? sizeof(double) : 0) + narrow);
+}
+
+// Without memory for the layout the handle keeps its row tiles; so it does
+// where less than half of the device's memory would stay free, so that
+// handles and vectors made later find what they would without the layouts.
 static void add_layouts(Uploader &U, DevMatrix &M, const int32_t *row_ptr, const Layouts &L,
                         const std::vector<TileDesc> &long_desc) {
     if (!L.has_jag && !L.has_sweep) return;
+    size_t free = 0, total = 0;
+    if (hipMemGetInfo && hipMemGetInfo(&free, &total) == hipSuccess && free < total / 2 + layout_bytes(M, L)) return;
     const DevMatrix before = M;
     const size_t keep = U.A->allocs.size();
     const int64_t bytes = U.A->bytes;

@@ -21,6 +21,14 @@
 
 extern "C" const char *mock_launch_log(void);
 
+// Device memory as the runtime reports it.
+static size_t mem_free = 0, mem_total = 0;
+extern "C" int hipMemGetInfo(size_t *free, size_t *total) {
+    *free = mem_free ? mem_free : size_t(1) << 40;
+    *total = mem_total ? mem_total : size_t(1) << 40;
+    return 0;
+}
+
 // Threads started while the library's capture gate was held.
 static std::atomic<int> started{0}, under_gate{0};
 
@@ -196,6 +204,26 @@ void plans_without_gate() {
     spmv_destroy(M);
 }
 
+// A layout is added only while half of the device's memory stays free.
+void layout_memory() {
+    const Csr A = banded(70'000, 70'000, 0);
+    mem_total = size_t(1) << 30;
+    int64_t bytes[4];
+    const size_t frees[4] = {size_t(1) << 30, (size_t(1) << 29) + (size_t(9) << 20), (size_t(1) << 29) + (size_t(16) << 20), 1};
+    for (int i = 0; i < 4; ++i) {
+        mem_free = frees[i];
+        spmv_matrix *M = nullptr;
+        spmv_info info{};
+        check(A.create(nullptr, 0, &M) == SPMV_OK && spmv_get_info(M, &info) == SPMV_OK, "create");
+        bytes[i] = info.device_bytes;
+        std::printf("  free %zu MB: %lld bytes\n", frees[i] >> 20, (long long)bytes[i]);
+        spmv_destroy(M);
+    }
+    // 12.1 MB of layout
+    check(bytes[0] > 20 * (int64_t)A.col.size() && bytes[2] == bytes[0], "a layout where there is room");
+    check(bytes[1] < 13 * (int64_t)A.col.size() && bytes[3] == bytes[1], "none where half would not stay free");
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -204,6 +232,7 @@ int main(int argc, char **argv) {
     else if (what == "sweep_rounds") sweep_rounds();
     else if (what == "wide_matrix") wide_matrix();
     else if (what == "plans_without_gate") plans_without_gate();
+    else if (what == "layout_memory") layout_memory();
     else ++failures;
     return failures ? 1 : 0;
 }

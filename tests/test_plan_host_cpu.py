@@ -55,3 +55,7 @@ def test_plan_memory_of_a_wide_matrix(driver):
 def test_layouts_are_planned_outside_the_capture_gate(driver):
     # the gate also holds back every graph capture of the process
     run(driver, "plans_without_gate")
+
+
+def test_layouts_leave_half_of_the_memory_free(driver):
+    run(driver, "layout_memory")
