@@ -222,9 +222,16 @@ static int apply_typed(const spmv_matrix *A, const V *val, const X *x, Y *y, voi
     return SPMV_OK;
 }
 
-// The k-vector product's tiles: the rows outside the long ones, cut to both
-// limits of kSpmmEntries.
+// The k-vector product's tiles: the plan's segments outside the long rows, cut
+// to both limits of kSpmmEntries.  Where that gives the plan's own tiles (every
+// plan of 1,024-entry tiles) they are shared.
 static int upload_spmm(Uploader &U, DevMatrix &M, const Plan &P, const int32_t *row_ptr) {
+    const auto is_list = [&P](const std::vector<TileDesc> &v, const std::vector<int32_t> &list) {
+        if (v.size() != list.size()) return false;
+        for (size_t i = 0; i < v.size(); ++i)
+            if (v[i].r0 != P.seg_bound[list[i]] || v[i].r1 != P.seg_bound[list[i] + 1]) return false;
+        return true;
+    };
     for (int l = 0; l < 2; ++l) {
         SpmmTiles &T = M.spmm[l];
         std::vector<TileDesc> v;
@@ -244,7 +251,9 @@ static int upload_spmm(Uploader &U, DevMatrix &M, const Plan &P, const int32_t *
         }
         T.n = (int32_t)v.size();
         if (v.empty()) continue;
-        if (int rc = U.put(&T.desc, v.data(), v.size(), 0)) return rc;
+        if (is_list(v, P.stream_list)) T.desc = M.stream_desc;
+        else if (is_list(v, P.cwin_list)) T.desc = M.cwin_desc;
+        else if (int rc = U.put(&T.desc, v.data(), v.size(), 0)) return rc;
     }
     return SPMV_OK;
 }
@@ -627,7 +636,6 @@ static int create_csr(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t
         if (!rc && !P.lidx12.empty()) rc = U.put(&M.lidx12, P.lidx12.data(), P.lidx12.size(), 0);
         else if (!rc) rc = U.put(&M.lidx, P.lidx.data(), P.lidx.size(), nz_pad);
     }
-    A->n_win_tiles = (int32_t)P.win_list.size();
     for (int32_t sg = 0; sg < P.n_seg(); ++sg)
         if (P.seg_kind[sg] != SEG_LONG)
             A->max_tile_entries = std::max(A->max_tile_entries,

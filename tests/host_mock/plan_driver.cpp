@@ -224,6 +224,34 @@ void layout_memory() {
     check(bytes[1] < 13 * (int64_t)A.col.size() && bytes[3] == bytes[1], "none where half would not stay free");
 }
 
+// A served matrix takes no more than the server counted for it: a budget of
+// exactly that and one request's vectors serves it again and again.
+void served_budget() {
+    Csr A;  // one entry a row: the most tiles per entry
+    A.n_cols = 200'000;
+    for (int32_t i = 0; i < A.n_cols; ++i) A.row({i});
+    const uint64_t n = (uint64_t)A.n, padded = n + 16;  // entries and the arrays' padding
+    srv_config cfg{};
+    cfg.n_slots = 1;
+    cfg.hbm_budget_bytes = 4 * (n + 1) + 12 * padded + 64 * (n / 512 + 16) + 16 * n;
+    spmv_server *S = nullptr;
+    int32_t id = -1;
+    check(srv_create(&cfg, &S) == SPMV_OK, "server");
+    check(srv_add_matrix(S, A.n, A.n_cols, (int64_t)n, A.row_ptr.data(), A.col.data(), A.val.data(), &id) == SPMV_OK, "matrix");
+    std::vector<double> x(n, 1.0), y(n);
+    for (int i = 0; i < 3; ++i) {
+        uint64_t ticket = 0;
+        srv_result r{};
+        check(srv_submit(S, id, SRV_SPMV, 1, x.data(), y.data(), 0.0, 0, &ticket) == SPMV_OK, "submit");
+        (void)srv_wait(S, ticket, &r);
+        check(r.done && r.status == SPMV_OK, (std::string("request served ") + r.message).c_str());
+    }
+    srv_stats st{};
+    (void)srv_get_stats(S, &st);
+    std::printf("  used %lld of %llu bytes\n", (long long)st.used_bytes, (unsigned long long)cfg.hbm_budget_bytes);
+    (void)srv_destroy(S);
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -233,6 +261,7 @@ int main(int argc, char **argv) {
     else if (what == "wide_matrix") wide_matrix();
     else if (what == "plans_without_gate") plans_without_gate();
     else if (what == "layout_memory") layout_memory();
+    else if (what == "served_budget") served_budget();
     else ++failures;
     return failures ? 1 : 0;
 }

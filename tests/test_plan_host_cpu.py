@@ -59,3 +59,7 @@ def test_layouts_are_planned_outside_the_capture_gate(driver):
 
 def test_layouts_leave_half_of_the_memory_free(driver):
     run(driver, "layout_memory")
+
+
+def test_served_matrices_stay_within_the_bytes_counted_for_them(driver):
+    run(driver, "served_budget")
