@@ -22,6 +22,7 @@ template <typename V, typename T> struct BsrArgs {
     int32_t n_tiles;
     int32_t per_xcd;
     int32_t chunk_log2;     // XCD assignment of tiles (xcd_tile)
+    int32_t streams;        // the blocks read, of this value type, stream from HBM
     int32_t ldx, ldy, off;  // leading dimensions and first column of this launch
 };
 

@@ -422,15 +422,17 @@ static void launch_k(BsrArgs<V, T> g, int grid, hipStream_t st) {
                          g.ldx % kW == 0 && g.ldy % kW == 0 && g.off % kW == 0;
         if (vec) {
             // Y rows of 16 bytes that this launch writes whole go past L2,
-            // which leaves it to X, where the matrix streams from HBM (1.7M
-            // block rows: FP64 k = 2 268 -> 247 us, FP32 k = 4 167.4 -> 159.3;
-            // 339K block rows, in cache: 55.9 -> 56.6 and 38.1 -> 38.6, 62K:
+            // which leaves it to X, where the blocks stream from HBM (1.7M
+            // block rows, inputs in turn: FP64 k = 2 268 -> 247 us, FP32 k = 4 167.4
+            // -> 161.4; one X and Y again and again 258 -> 253 and 160 -> 164;
+            // FP32 blocks that the memory-side cache keeps, 512K block rows k = 4:
+            // 52.6 -> 54.2; 339K block rows: 55.9 -> 56.6 and 38.1 -> 38.6, 62K:
             // 13.2 -> 13.6 and 10.5 -> 10.8).  Wider rows and rows written by
             // several launches were slower so (1.7M block rows: FP64 k = 4
             // 305 -> 313 us, FP32 k = 5 / 8 / 16 332 / 232 / 693 -> 343 / 244 / 726),
             // rows of 8 bytes and one column equal.
             if constexpr (K * sizeof(T) == 16) {
-                if (g.ldy == K && g.chunk_log2 >= 0) {
+                if (g.ldy == K && g.streams) {
                     hipLaunchKernelGGL((k_bsr3<V, T, K, true, true>), dim3(grid), dim3(kBlock), 0, st, g);
                     return;
                 }
@@ -458,6 +460,7 @@ hipError_t launch_bsr3(const DevMatrix &M, const V *val, int k, const T *X, T *Y
     g.ldy = k;
     g.per_xcd = M.xcd_remap && M.n_bsr_tiles >= 16 ? (M.n_bsr_tiles + 7) / 8 : 0;
     g.chunk_log2 = M.xcd_chunk_log2;
+    g.streams = (9 * sizeof(V) + sizeof(int32_t)) * (size_t)M.nnz >= ((size_t)256 << 20);
     const int grid = xcd_grid(M.n_bsr_tiles, g.per_xcd, g.chunk_log2);
     // right-hand sides in chunks of 8, 4, 2, 1 columns
     int off = 0;
