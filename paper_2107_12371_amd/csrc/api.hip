@@ -564,6 +564,9 @@ static int create_csr(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t
     if (rc) return rc;
     Layouts L;
     plan_layouts(n_rows, n_cols, nnz, row_ptr, col_idx, P, flags, params, L);
+    // (with fewer entries the k-vector product makes no use of it)
+    const bool x_spread = !P.long_list.empty() ||
+                          (nnz >= (1 << 16) && lines_per_entry(n_rows, row_ptr, col_idx, P.tile_nnz - 3, 8) >= 0.5);
 
     auto *A = new (std::nothrow) spmv_matrix();
     if (!A) return fail(SPMV_ENOMEM, "host allocation failed");
@@ -582,6 +585,7 @@ static int create_csr(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t
     M.n_rows = n_rows;
     M.n_cols = n_cols;
     M.nnz = nnz;
+    M.x_spread = x_spread;
     M.tile_nnz = P.tile_nnz;
     M.ring_words = P.ring_words;
     M.xcd_remap = !(flags & SPMV_NO_XCD_REMAP) && P.xcd_chunk != -1;

@@ -79,6 +79,7 @@ struct DevMatrix {
     uint16_t *lidx = nullptr;        // window-relative column per stored entry (+ padding)
     uint32_t *lidx12 = nullptr;      // 2048-entry tiles: packed 12-bit positions per tile and lane
     SpmmTiles spmm[2];               // tiles of the k-vector product (spmm.hip)
+    bool x_spread = false;           // each XCD gathers from all of x (scattered columns, long rows)
     // jagged window tiles (jag.hip), for the value types that have a copy of
     // the values in that order
     int32_t n_jag = 0, jag_stride = 0, jag_width = 0, jag_groups = 0;

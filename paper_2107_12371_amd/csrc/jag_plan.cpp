@@ -179,13 +179,11 @@ bool build_jag_plan(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *
     return true;
 }
 
-// Distinct 128-byte lines of x per stored entry in blocks of 256 rows, over
-// about 32 blocks spread evenly (1: every gather a line of its own).
-static double lines_per_entry(int32_t n_rows, const int32_t *row_ptr, const int32_t *col_idx, int long_len) {
+double lines_per_entry(int32_t n_rows, const int32_t *row_ptr, const int32_t *col_idx, int long_len, int blocks) {
     int64_t lines = 0, entries = 0;
     std::vector<int32_t> u;
-    const int32_t blocks = (n_rows + 255) / 256, step = std::max(1, blocks / 32);
-    for (int32_t b = 0; b < blocks; b += step) {
+    const int32_t all = (n_rows + 255) / 256, step = std::max(1, all / blocks);
+    for (int32_t b = 0; b < all; b += step) {
         u.clear();
         for (int32_t r = b * 256; r < std::min(n_rows, b * 256 + 256); ++r)
             if (row_ptr[r + 1] - row_ptr[r] <= long_len)
@@ -200,7 +198,7 @@ static double lines_per_entry(int32_t n_rows, const int32_t *row_ptr, const int3
 bool build_sweep_plan(int32_t n_rows, int32_t n_cols, const int32_t *row_ptr, const int32_t *col_idx, int long_len,
                       int n_cus, SweepPlan &S) {
     S = SweepPlan{};
-    if (lines_per_entry(n_rows, row_ptr, col_idx, long_len) < 0.75) return false;
+    if (lines_per_entry(n_rows, row_ptr, col_idx, long_len, 32) < 0.75) return false;
     const auto len_of = [row_ptr](int32_t r) { return row_ptr[r + 1] - row_ptr[r]; };
     // entries of the runs of rows between long rows: a tile ends with its run
     std::vector<int64_t> run;

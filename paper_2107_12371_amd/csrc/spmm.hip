@@ -230,28 +230,35 @@ static void launch_tiles(const DevMatrix &M, const double *X, double *Y, int k, 
     const bool pieces = vec && (reinterpret_cast<uintptr_t>(Y) & 15) == 0;
     const size_t x_bytes = sizeof(double) * (size_t)M.n_cols * (size_t)k;
     const bool off32 = x_bytes < ((size_t)1 << 32);
-    // The stream goes past the caches where they cannot keep it for the next
-    // product on the handle: from 272 MB of matrix and X on, a little over the
-    // 256 MB memory-side cache (one matrix, ordinary / non-temporal loads: 1M-row
-    // 27-point mesh k = 2 47 / 60 us, k = 8 (256 MB) 81 / 100, k = 12 (287 MB) 148 / 146;
-    // 2M-row kNN mesh k = 4 (226 MB) 51 / 72, k = 8 (287 MB) 116 / 106; 4M-row 27-point
-    // mesh k = 8 398 / 389), and where the matrix would fit the XCDs' L2s but for
-    // X (262K-row kNN mesh, 21 MB, k = 2 5.9 / 7.7, k = 8 13.9 / 12.0; 125K-row 27-point
-    // mesh, 25 MB, k = 4 7.9 / 8.0, k = 8 12.3 / 11.5; 512K-row kNN mesh, 40 MB, k = 8
-    // 23.2 / 29.3).
-    const size_t stream = matrix_bytes(M) + x_bytes;
-    const int stream_nt = stream > ((size_t)272 << 20) || (matrix_bytes(M) <= kL2Bytes && stream > kL2Bytes);
     // Y past L2, but for the smallest (49K-row tet mesh k = 2 3.16 us ordinary,
     // 3.31 non-temporal, k = 8 4.97 / 4.80; 125K-row kNN mesh k = 8 7.5 / 6.6; 1M-row
     // 27-point mesh k = 8 104 / 81)
-    const bool y_nt = sizeof(double) * (size_t)M.n_rows * (size_t)k >= ((size_t)2 << 20);
+    const size_t y_bytes = sizeof(double) * (size_t)M.n_rows * (size_t)k;
+    const bool y_nt = pieces && y_bytes >= ((size_t)2 << 20);
+    // The stream goes past the caches where they cannot keep it for the next
+    // product on the handle: from 272 MB of matrix, X and a Y that passes
+    // through them on, a little over the 256 MB memory-side cache (one matrix,
+    // ordinary / non-temporal loads: 1M-row 27-point mesh k = 2 47 / 60 us, k = 8
+    // (256 MB) 81 / 100, k = 12 (287 MB) 148 / 146; 2M-row kNN mesh k = 4 (226 MB) 51 / 72,
+    // k = 5 (313 MB) 117 / 108, k = 8 (287 MB) 116 / 106; 4M-row 27-point mesh k = 8
+    // 398 / 389).  And where an XCD's L2 would hold its share of X but
+    // for its share of the matrix: where the L2s hold the matrix alone (262K-row
+    // kNN mesh, 21 MB, k = 2 5.9 / 7.7, k = 8 13.9 / 12.0; 125K-row 27-point mesh, 25 MB,
+    // k = 4 7.9 / 8.0, k = 8 12.3 / 11.5; 512K-row kNN mesh, 40 MB, k = 8 23.2 / 29.3), or
+    // each XCD gathers from all of a small X (random order: 125K-row kNN mesh k = 2
+    // 6.3 / 7.7, k = 3 10.5 / 9.7; 125K-row 27-point mesh k = 2 14.7 / 13.1; 512K rows k = 2,
+    // X of 8 MB, 85 / 79, k = 3 120 / 120; 125K-row kNN mesh with 3 long rows k = 3
+    // 26.6 / 18.5).
+    const size_t matrix = matrix_bytes(M), share = matrix / 8 + (M.x_spread ? x_bytes : x_bytes / 8);
+    const int stream_nt = matrix + x_bytes + (y_nt ? 0 : y_bytes) > ((size_t)272 << 20) ||
+                          (share > kL2Bytes / 8 && (M.x_spread ? x_bytes <= ((size_t)12 << 20) : matrix <= kL2Bytes));
     const auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), lds, st, T.desc, T.n, per_xcd, chunk_log2,
                            M.row_ptr, M.col, M.val64, X, Y, k, T.entries, stream_nt);
     };
-    if (pieces && off32 && y_nt) go(k_spmm_tiles<KC, U, true, true, Y_PIECES_NT>);
+    if (y_nt && off32) go(k_spmm_tiles<KC, U, true, true, Y_PIECES_NT>);
     else if (pieces && off32) go(k_spmm_tiles<KC, U, true, true, Y_PIECES>);
-    else if (pieces) go(k_spmm_tiles<KC, U, true, false, Y_PIECES_NT>);
+    else if (pieces) go(k_spmm_tiles<KC, U, true, false, Y_PIECES_NT>);  // X of 4 GB and more
     else if (vec && off32) go(k_spmm_tiles<KC, U, true, true, Y_WORDS>);
     else if (vec) go(k_spmm_tiles<KC, U, true, false, Y_WORDS>);
     else if (off32) go(k_spmm_tiles<KC, U, false, true, Y_WORDS>);
@@ -290,8 +297,10 @@ hipError_t launch_spmm(const spmv_matrix *A, const double *X, double *Y, int k, 
         // (4M-row 27-point mesh k = 8 389 us with eight, 402 with four; 262K rows,
         // 56 MB, k = 2 16.4 / 17.7, k = 3 25.2 / 24.4, k = 8 22.4 / 22.9; 125K rows, 26 MB,
         // k = 2 7.0 / 5.9, k = 8 13.1 / 12.3; 4M-row kNN mesh, 7 entries per row, k = 8
-        // 254 / 236).
-        if (k % 2 == 0 && matrix_bytes(M) > kL2Bytes && M.nnz >= 16 * (int64_t)M.n_rows)
+        // 254 / 236); where each XCD gathers from all of x, only for matrices that
+        // stream from HBM (512K-row 27-point mesh in random order k = 2 86 / 80).
+        const bool large = M.x_spread ? M.xcd_chunk_log2 >= 0 : matrix_bytes(M) > kL2Bytes;
+        if (k % 2 == 0 && large && M.nnz >= 16 * (int64_t)M.n_rows)
             launch_tiles<2, 8>(M, X, Y, k, st);
         else launch_tiles<2, 4>(M, X, Y, k, st);
     }
