@@ -20,7 +20,8 @@
 // workgroups form beta (so p is read once for both); with more than 4,096
 // SpMV partials their first-stage sums are a launch of their own (four).
 // All scalars live on the device;
-// every kernel returns at once when the device flag `done` is set, so a
+// every kernel does no work when the device flag `done` is set (some have
+// issued their first loads by the time they know), so a
 // captured graph of several iterations can be replayed blindly and the host
 // synchronises once per replay.  Reductions are two-stage with a fixed
 // partition and a fixed order, so a solve is bitwise reproducible.
@@ -671,7 +672,7 @@ __global__ __launch_bounds__(kBlock) void k_cg1(const TileDesc *__restrict__ des
 
 // The x/r update of a fused iteration: p_new = r + beta p (as the fused
 // product formed it) is written for this workgroup's rows, then x += alpha
-// p_new, r -= alpha q and the r.r partial, as k_update_xr.  Workgroup 0
+// p_new, r -= alpha q and the r.r partial.  Workgroup 0
 // clears F_FRESH.  The fused path runs on at most 1,024 workgroups, so a
 // workgroup's chunk holds at most 1,024 rows, four per lane: the state, the
 // p.q partials and all of the lane's vector elements are loaded before any

@@ -99,7 +99,7 @@ constexpr int kPackLanes = 256;     // lanes per workgroup; each lane owns 4 ent
 // Jagged window tiles (jag.hip): up to kJagRows consecutive rows of at most
 // kJagMaxLen entries each, sorted by length and cut into slices of one
 // wavefront; windows of at most kJagMaxSectors sectors of kJagSector words,
-// so that 12 bits hold a position. 
+// so that 12 bits hold a position.
 constexpr int kJagSlice = 64;
 // Matrices with fewer stored entries keep the row tiles alone: one launch
 // takes 2.4-3.2 us there and the row tiles' workgroups, being smaller, fill

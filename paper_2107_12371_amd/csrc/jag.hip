@@ -19,14 +19,18 @@
 // go straight to LDS (16 bytes per lane, no registers) and every position
 // and value load of the slice goes out behind them: the second round trip.
 // The rest is LDS reads and adds.  The row tiles (k_stream, k_cwin) need
-// three round trips and about 26 vector instructions per entry and lane,
-// many of them to move products through LDS; this kernel needs about 6.  A
+// three round trips and move products through LDS: on the 16M-row 27-point
+// mesh in FP32 k_cwin issues 26.5 vector instructions per entry and lane, this
+// kernel 11.9 (on short rows it issues the more, 21.6 against k_stream's 13.7 on
+// the kNN mesh in FP64, and is faster all the same).  A
 // version that took the runs' lengths from the lanes (four round trips) was
 // 8-10% slower.  The slices of a tile share a window because a wider tile
 // needs fewer words per row: 128 rows per tile were 5-9% slower, 512 rows
 // within 1.5% (and their windows pass 4,096 words on the 27-point mesh).
 // Non-temporal value loads were slower (a run's ends share their cache lines
-// with the next run), non-temporal y stores 2-4% faster.
+// with the next run), non-temporal y stores 2-4% faster, also where a solver's
+// next kernel reads y: the BF16 polynomial's product, solves on 91K to 8M rows,
+// within 1% either way (and so for the sweep tiles).
 // Measured, row tiles -> jagged tiles, three matrices in turn: kNN mesh, 2M
 // rows, FP64 42.1 -> 35.5 us; 27-point mesh, 4M rows, FP32 81.0 -> 77.7 us
 // and BF16 73.2 -> 68.0 us; one matrix kept in cache, 1M rows of the 27-point

@@ -87,8 +87,8 @@ enum YStore : int { Y_WORDS, Y_PIECES, Y_PIECES_NT };
 
 // Tasks are (row, group of KC columns); a lane takes U entries of its row per
 // round.  What bounds it: the L1s, whose gathers of adjacent rows wait for the
-// same lines (busy in 50% of the cycles, stalled on lines under way in 39% at
-// k = 8), and the rounds' latencies.  So a tile is about one task per lane,
+// same lines (16M rows, k = 8: a line looked up in 51% of the cycles, stalled on
+// lines under way in 39%), and the rounds' latencies.  So a tile is about one task per lane,
 // the row bounds are staged with the entries, the rounds but the last need
 // neither clamps nor selects, and rows keep their order: sorted by length they
 // take fewer rounds, but adjacent rows share lines (4M-row 27-point mesh, k = 8:

@@ -20,7 +20,7 @@
 //    in that L2.
 //  * k_cwin    compact windows: the tile's distinct columns, merged into at
 //    most 64 runs, are staged in LDS with contiguous loads and entries read
-//    x there through 16-bit window positions (default for large FP64
+//    x there through 12- or 16-bit window positions (default for large FP64
 //    products).  Tiles whose window does not fit run as in k_stream inside
 //    the same launch.
 //  * k_pipe, k_wave  persistent variants of k_stream (per workgroup and per
@@ -31,6 +31,8 @@
 //  * k_window  the paper's circular cache taken literally: one workgroup
 //    walks a block of adjacent tiles in order, staging into an LDS ring only
 //    the x words the previous tiles did not bring in.
+// Products of mid-size matrices, of FP32 and BF16 values and of scattered
+// columns take the tiles of jag.hip and sweep.hip by default.
 // Every y_i is summed in an order fixed by the plan alone, so results are
 // bitwise reproducible, the same for every kernel choice, and independent of
 // what else runs on the GPU.
@@ -667,9 +669,9 @@ static hipError_t launch_nt(const DevMatrix &M, SpmvArgs<V, X, Y> g, hipStream_t
         a.chunk_log2 = M.xcd_chunk_log2;
         if (M.xcd_remap && M.n_cwin >= 16) a.per_xcd = (M.n_cwin + 7) / 8;
         const int grid = xcd_grid(M.n_cwin, a.per_xcd, a.chunk_log2);
-        // every value type goes through the windows (16M-row mesh matrix,
-        // with the popcount run lookup: FP64 0.567 vs 0.73 ms direct, FP32
-        // 0.327 vs 0.48, bfloat16 0.292 vs 0.405)
+        // binary64 products, and those of narrower values on handles without
+        // jagged tiles (16M-row mesh matrix, with the popcount run lookup: FP64
+        // 0.567 vs 0.73 ms direct, FP32 0.327 vs 0.48, bfloat16 0.292 vs 0.405)
         if (M.kernel == KV_PIPELINED && M.n_cwin >= 64) {
             a.per_xcd = (M.n_cwin + 7) / 8;
             a.chunk_log2 = -1;
