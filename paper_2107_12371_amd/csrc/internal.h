@@ -147,9 +147,10 @@ struct SweepPlan {
 bool build_sweep_plan(int32_t n_rows, int32_t n_cols, const int32_t *row_ptr, const int32_t *col_idx, int long_len,
                       int n_cus, SweepPlan &S);
 
-// Distinct 128-byte lines of x per stored entry in about `blocks` blocks of 256
-// rows spread evenly (1: every gather a line of its own).
-double lines_per_entry(int32_t n_rows, const int32_t *row_ptr, const int32_t *col_idx, int long_len, int blocks);
+// Distinct 128-byte lines of x per stored entry in about `blocks` blocks of
+// `rows` rows spread evenly (1: every gather a line of its own).
+double lines_per_entry(int32_t n_rows, const int32_t *row_ptr, const int32_t *col_idx, int long_len, int rows,
+                       int blocks);
 
 // Sliced ELLPACK with sigma sorting (SELL-C-sigma; the paper's sliced
 // ELLPACK storage, Sec. 4.2, with C = 64 rows per slice, one per lane of a

@@ -179,13 +179,14 @@ bool build_jag_plan(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *
     return true;
 }
 
-double lines_per_entry(int32_t n_rows, const int32_t *row_ptr, const int32_t *col_idx, int long_len, int blocks) {
+double lines_per_entry(int32_t n_rows, const int32_t *row_ptr, const int32_t *col_idx, int long_len, int rows,
+                       int blocks) {
     int64_t lines = 0, entries = 0;
     std::vector<int32_t> u;
-    const int32_t all = (n_rows + 255) / 256, step = std::max(1, all / blocks);
+    const int32_t all = (int32_t)(((int64_t)n_rows + rows - 1) / rows), step = std::max(1, all / blocks);
     for (int32_t b = 0; b < all; b += step) {
         u.clear();
-        for (int32_t r = b * 256; r < std::min(n_rows, b * 256 + 256); ++r)
+        for (int32_t r = b * rows; r < n_rows && r - b * rows < rows; ++r)
             if (row_ptr[r + 1] - row_ptr[r] <= long_len)
                 for (int32_t k = row_ptr[r]; k < row_ptr[r + 1]; ++k) u.push_back(col_idx[k] / 16);
         entries += (int64_t)u.size();
@@ -198,7 +199,7 @@ double lines_per_entry(int32_t n_rows, const int32_t *row_ptr, const int32_t *co
 bool build_sweep_plan(int32_t n_rows, int32_t n_cols, const int32_t *row_ptr, const int32_t *col_idx, int long_len,
                       int n_cus, SweepPlan &S) {
     S = SweepPlan{};
-    if (lines_per_entry(n_rows, row_ptr, col_idx, long_len, 32) < 0.75) return false;
+    if (lines_per_entry(n_rows, row_ptr, col_idx, long_len, 256, 32) < 0.75) return false;
     const auto len_of = [row_ptr](int32_t r) { return row_ptr[r + 1] - row_ptr[r]; };
     // entries of the runs of rows between long rows: a tile ends with its run
     std::vector<int64_t> run;
