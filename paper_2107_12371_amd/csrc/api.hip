@@ -76,7 +76,11 @@ struct Uploader {
     hipError_t init = hipSuccess;
 
     explicit Uploader(spmv_matrix *A_) : A(A_) { init = hipStreamCreateWithFlags(&s, hipStreamNonBlocking); }
+    // Without keep (a failed creation, or an exception on its way) what was
+    // allocated goes with it.
+    bool keep = false;
     ~Uploader() {
+        if (!keep) release_all();
         if (s) (void)hipStreamDestroy(s);
     }
     Uploader(const Uploader &) = delete;
@@ -150,7 +154,6 @@ struct Uploader {
         A->bytes = bytes;
     }
 
-    // Releases what was allocated so far (failed creation).
     void release_all() {
         for (void *q : A->allocs) (void)hipFree(q);
         A->allocs.clear();
@@ -455,18 +458,13 @@ static int create_sell(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_
     SellPlan S;
     int rc = build_sell_plan(n_rows, row_ptr, p.sell_sigma, S);
     if (rc) return rc;
-    auto *A = new (std::nothrow) spmv_matrix();
+    std::unique_ptr<spmv_matrix> own(new (std::nothrow) spmv_matrix());
+    spmv_matrix *A = own.get();
     if (!A) return fail(SPMV_ENOMEM, "host allocation failed");
     hipError_t e = hipGetDevice(&A->device);
-    if (e != hipSuccess) {
-        delete A;
-        return hip_fail(e, "hipGetDevice");
-    }
+    if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
     Uploader U(A);
-    if (U.init != hipSuccess) {
-        delete A;
-        return hip_fail(U.init, "upload stream");
-    }
+    if (U.init != hipSuccess) return hip_fail(U.init, "upload stream");
     DevMatrix &M = A->M;
     M.format = SPMV_FORMAT_SELL;
     M.long_split = p.long_rows == 0;
@@ -523,11 +521,7 @@ static int create_sell(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_
     }
     M.n_seg = M.n_sell_wg + M.n_long;
     if (!rc) prepare_launch_queries();
-    if (rc) {
-        U.release_all();
-        delete A;
-        return rc;
-    }
+    if (rc) return rc;
     spmv_info &I = A->info;
     std::memset(&I, 0, sizeof I);
     I.n_rows = n_rows;
@@ -545,7 +539,8 @@ static int create_sell(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_
     I.n_long_pieces = M.n_long_pieces;
     I.workspace_bytes = workspace_bytes_of(M);
     I.y_scratch_ok = M.piece_long && M.long_split && (int64_t)M.y_ws_rows >= M.n_long_pieces;
-    *out = A;
+    U.keep = true;
+    *out = own.release();
     return SPMV_OK;
 }
 
@@ -569,18 +564,13 @@ static int create_csr(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t
     const bool x_spread = !P.long_list.empty() ||
                           (nnz >= (1 << 16) && lines_per_entry(n_rows, row_ptr, col_idx, P.tile_nnz - 3, 64, 8) >= 0.5);
 
-    auto *A = new (std::nothrow) spmv_matrix();
+    std::unique_ptr<spmv_matrix> own(new (std::nothrow) spmv_matrix());
+    spmv_matrix *A = own.get();
     if (!A) return fail(SPMV_ENOMEM, "host allocation failed");
     hipError_t e = hipGetDevice(&A->device);
-    if (e != hipSuccess) {
-        delete A;
-        return hip_fail(e, "hipGetDevice");
-    }
+    if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
     Uploader U(A);
-    if (U.init != hipSuccess) {
-        delete A;
-        return hip_fail(U.init, "upload stream");
-    }
+    if (U.init != hipSuccess) return hip_fail(U.init, "upload stream");
     DevMatrix &M = A->M;
     M.long_split = !params || params->long_rows == 0;
     M.n_rows = n_rows;
@@ -652,11 +642,7 @@ static int create_csr(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t
         hipError_t e2 = prepare_window_kernels();
         if (e2 != hipSuccess) rc = hip_fail(e2, "window kernel LDS opt-in");
     }
-    if (rc) {
-        U.release_all();
-        delete A;
-        return rc;
-    }
+    if (rc) return rc;
     spmv_info &I = A->info;
     std::memset(&I, 0, sizeof I);
     I.n_rows = n_rows;
@@ -680,13 +666,13 @@ static int create_csr(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t
     I.n_long_pieces = M.n_long_pieces;
     I.workspace_bytes = workspace_bytes_of(M);
     I.y_scratch_ok = M.piece_long && M.long_split && (int64_t)M.y_ws_rows >= M.n_long_pieces;
-    *out = A;
+    U.keep = true;
+    *out = own.release();
     return SPMV_OK;
 }
 
-extern "C" int spmv_create(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *row_ptr,
-                           const int32_t *col_idx, const double *values, uint32_t flags,
-                           const spmv_params *params, spmv_matrix **out) {
+static int create_matrix(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *row_ptr, const int32_t *col_idx,
+                         const double *values, uint32_t flags, const spmv_params *params, spmv_matrix **out) {
     clear_error();
     if (!out) return fail(SPMV_EINVAL, "out is NULL");
     *out = nullptr;
@@ -708,8 +694,8 @@ extern "C" int spmv_create(int32_t n_rows, int32_t n_cols, int64_t nnz, const in
         }
         if (!rc) rc = fetch_device(values, (size_t)nnz, va, "values");
         if (rc) return rc;
-        return spmv_create(n_rows, n_cols, nnz, rp.data(), nnz ? ci.data() : nullptr, nnz ? va.data() : nullptr,
-                           flags & ~SPMV_DEVICE_PTRS, params, out);
+        return create_matrix(n_rows, n_cols, nnz, rp.data(), nnz ? ci.data() : nullptr, nnz ? va.data() : nullptr,
+                             flags & ~SPMV_DEVICE_PTRS, params, out);
     }
     int rc = validate_csr(n_rows, n_cols, nnz, row_ptr, col_idx);
     if (rc) return rc;
@@ -719,6 +705,17 @@ extern "C" int spmv_create(int32_t n_rows, int32_t n_cols, int64_t nnz, const in
         return create_sell(n_rows, n_cols, nnz, row_ptr, col_idx, values, flags, *params, out);
     }
     return create_csr(n_rows, n_cols, nnz, row_ptr, col_idx, values, false, flags, params, out);
+}
+
+extern "C" int spmv_create(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *row_ptr,
+                           const int32_t *col_idx, const double *values, uint32_t flags,
+                           const spmv_params *params, spmv_matrix **out) {
+    // no exception leaves a C entry: the plans' vectors may find no host memory
+    try {
+        return create_matrix(n_rows, n_cols, nnz, row_ptr, col_idx, values, flags, params, out);
+    } catch (const std::exception &) {
+        return fail(SPMV_ENOMEM, "host allocation failed");
+    }
 }
 
 extern "C" int spmv_destroy(spmv_matrix *A) {
@@ -877,18 +874,13 @@ extern "C" int spmv_create_bsr3(int32_t n_block_rows, int32_t n_block_cols, int6
         return fail(SPMV_EINVAL, "scalar dimension exceeds int32");
     if (nnz_blocks > 0 && !bvalues) return fail(SPMV_EINVAL, "bvalues is NULL with nnz_blocks > 0");
     std::vector<int32_t> tiles = build_bsr_tiles(n_block_rows, brow_ptr, kBsrRows, kBsrBlocks);
-    auto *A = new (std::nothrow) spmv_matrix();
+    std::unique_ptr<spmv_matrix> own(new (std::nothrow) spmv_matrix());
+    spmv_matrix *A = own.get();
     if (!A) return fail(SPMV_ENOMEM, "host allocation failed");
     hipError_t e = hipGetDevice(&A->device);
-    if (e != hipSuccess) {
-        delete A;
-        return hip_fail(e, "hipGetDevice");
-    }
+    if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
     Uploader U(A);
-    if (U.init != hipSuccess) {
-        delete A;
-        return hip_fail(U.init, "upload stream");
-    }
+    if (U.init != hipSuccess) return hip_fail(U.init, "upload stream");
     DevMatrix &M = A->M;
     M.block = 3;
     M.n_rows = n_block_rows;
@@ -908,11 +900,7 @@ extern "C" int spmv_create_bsr3(int32_t n_block_rows, int32_t n_block_cols, int6
     }
     M.n_bsr_tiles = (int32_t)tiles.size() - 1;
     if (!rc) rc = U.put(&M.bsr_tiles, tiles.data(), tiles.size(), 0);
-    if (rc) {
-        U.release_all();
-        delete A;
-        return rc;
-    }
+    if (rc) return rc;
     spmv_info &I = A->info;
     std::memset(&I, 0, sizeof I);
     I.n_rows = n_block_rows;
@@ -923,6 +911,7 @@ extern "C" int spmv_create_bsr3(int32_t n_block_rows, int32_t n_block_cols, int6
     I.has_fp32 = M.val32 != nullptr;
     I.device_bytes = A->bytes;
     I.block_size = 3;
-    *out = A;
+    U.keep = true;
+    *out = own.release();
     return SPMV_OK;
 }

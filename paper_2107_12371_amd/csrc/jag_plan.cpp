@@ -6,28 +6,12 @@
 #include <algorithm>
 #include <atomic>
 #include <cstring>
-#include <new>
-#include <system_error>
 #include <thread>
 
 #include "internal.h"
+#include "shares.h"
 
 namespace spmvlib {
-
-// Runs work(t) for t < n on up to n threads; a thread that cannot be started
-// has its share run here.
-template <typename F> static void run_shares(int n, F &&work) {
-    std::vector<std::thread> th;
-    int t = 1;
-    try {
-        th.reserve((size_t)n);
-        for (; t < n; ++t) th.emplace_back(work, t);
-    } catch (const std::exception &) {
-    }
-    work(0);
-    for (; t < n; ++t) work(t);
-    for (auto &x : th) x.join();
-}
 
 bool build_jag_plan(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *row_ptr, const int32_t *col_idx,
                     int long_len, JagPlan &J) {
@@ -55,46 +39,41 @@ bool build_jag_plan(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *
     std::vector<std::vector<int32_t>> lists(nth);
     std::vector<int64_t> off((size_t)n_cand, 0);
     std::vector<int32_t> count((size_t)n_cand, -1);  // sectors; -1: the window does not fit
-    std::atomic<bool> failed{false};
     std::atomic<int64_t> left_out{0};  // entries of tiles whose window does not fit
     run_shares(nth, [&](int t) {
-        try {
-            // a tile's sectors: at most kJagMaxSectors + 1 in a table of 1,024
-            // (a mark per sector of x would take n_cols / 2 bytes per thread)
-            constexpr uint32_t kSlots = 1024;
-            static_assert(2 * kJagMaxSectors <= kSlots, "half full at most, one more for the sector that is too many");
-            std::vector<int32_t> table(kSlots), u;
-            std::vector<int32_t> &out = lists[t];
-            // contiguous shares: the tiles' lists follow each other in order
-            const int32_t c0 = (int32_t)((int64_t)n_cand * t / nth), c1 = (int32_t)((int64_t)n_cand * (t + 1) / nth);
-            for (int32_t i = c0; i < c1; ++i) {
-                u.clear();
-                std::fill(table.begin(), table.end(), -1);
-                const int32_t s = row_ptr[first[i]], e = row_ptr[first[i] + rows[i]];
-                for (int32_t k = s; k < e && (int)u.size() <= kJagMaxSectors; ++k) {
-                    const int32_t sc = col_idx[k] / kJagSector;
-                    uint32_t at = (uint32_t)sc * 2654435769u >> 22;
-                    while (table[at] != sc && table[at] >= 0) at = (at + 1) % kSlots;
-                    if (table[at] != sc) {
-                        table[at] = sc;
-                        u.push_back(sc);
-                    }
+        // a tile's sectors: at most kJagMaxSectors + 1 in a table of 1,024
+        // (a mark per sector of x would take n_cols / 2 bytes per thread)
+        constexpr uint32_t kSlots = 1024;
+        static_assert(2 * kJagMaxSectors <= kSlots, "half full at most, one more for the sector that is too many");
+        std::vector<int32_t> table(kSlots), u;
+        std::vector<int32_t> &out = lists[t];
+        // contiguous shares: the tiles' lists follow each other in order
+        const int32_t c0 = (int32_t)((int64_t)n_cand * t / nth), c1 = (int32_t)((int64_t)n_cand * (t + 1) / nth);
+        for (int32_t i = c0; i < c1; ++i) {
+            u.clear();
+            std::fill(table.begin(), table.end(), -1);
+            const int32_t s = row_ptr[first[i]], e = row_ptr[first[i] + rows[i]];
+            for (int32_t k = s; k < e && (int)u.size() <= kJagMaxSectors; ++k) {
+                const int32_t sc = col_idx[k] / kJagSector;
+                uint32_t at = (uint32_t)sc * 2654435769u >> 22;
+                while (table[at] != sc && table[at] >= 0) at = (at + 1) % kSlots;
+                if (table[at] != sc) {
+                    table[at] = sc;
+                    u.push_back(sc);
                 }
-                if ((int)u.size() > kJagMaxSectors) {
-                    // more than the rule below allows: the rest need not be looked at
-                    if (8 * (left_out += e - s) > nnz - long_entries) return;
-                    continue;
-                }
-                std::sort(u.begin(), u.end());
-                off[i] = (int64_t)out.size();
-                count[i] = (int32_t)u.size();
-                out.insert(out.end(), u.begin(), u.end());
             }
-        } catch (const std::exception &) {
-            failed = true;
+            if ((int)u.size() > kJagMaxSectors) {
+                // more than the rule below allows: the rest need not be looked at
+                if (8 * (left_out += e - s) > nnz - long_entries) return;
+                continue;
+            }
+            std::sort(u.begin(), u.end());
+            off[i] = (int64_t)out.size();
+            count[i] = (int32_t)u.size();
+            out.insert(out.end(), u.begin(), u.end());
         }
     });
-    if (failed || 8 * left_out > nnz - long_entries) return false;
+    if (8 * left_out > nnz - long_entries) return false;
     // Worth it when nearly all of the entries that row tiles would work lie
     // in the tiles and the staged words do not outnumber them (a scattered
     // ordering touches a sector of 8 words per entry, and gathering x

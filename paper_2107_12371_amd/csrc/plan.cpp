@@ -24,6 +24,7 @@
 #include <cstring>
 
 #include "internal.h"
+#include "shares.h"
 
 #include <thread>
 
@@ -162,10 +163,7 @@ static void pack_lidx12(const int32_t *row_ptr, Plan &P) {
             }
         }
     };
-    std::vector<std::thread> th;
-    for (int t = 1; t < nth; ++t) th.emplace_back(work, t);
-    work(0);
-    for (auto &x : th) x.join();
+    run_shares(nth, work);
 }
 
 static int build_plan_once(int32_t n_rows, int32_t n_cols, int64_t nnz, const int32_t *row_ptr,
@@ -358,10 +356,7 @@ static int build_plan_once(int32_t n_rows, int32_t n_cols, int64_t nnz, const in
                 ok[sg] = t + 1;
             }
         };
-        std::vector<std::thread> th;
-        for (int t = 1; t < nth; ++t) th.emplace_back(work, t);
-        work(0);
-        for (auto &x : th) x.join();
+        run_shares(nth, work);
         std::vector<int64_t> base(nth, 0);
         int64_t tot = 0;
         for (int t = 0; t < nth; ++t) {

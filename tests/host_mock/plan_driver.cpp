@@ -9,6 +9,8 @@
 #include <atomic>
 #include <climits>
 #include <cstdint>
+#include <cstdlib>
+#include <new>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -28,6 +30,21 @@ extern "C" int hipMemGetInfo(size_t *free, size_t *total) {
     *total = mem_total ? mem_total : size_t(1) << 40;
     return 0;
 }
+
+// The countdown-th allocation of this thread from now on fails (0: none).
+static thread_local long fail_at = 0;
+static void *allocate(size_t n) {
+    if (fail_at > 0 && --fail_at == 0) return nullptr;
+    return std::malloc(n ? n : 1);
+}
+void *operator new(size_t n) {
+    void *p = allocate(n);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void *operator new(size_t n, const std::nothrow_t &) noexcept { return allocate(n); }
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
 
 // Threads started while the library's capture gate was held.
 static std::atomic<int> started{0}, under_gate{0};
@@ -252,6 +269,40 @@ void served_budget() {
     (void)srv_destroy(S);
 }
 
+// An allocation that fails anywhere in a creation (on the calling thread) is
+// SPMV_ENOMEM, or a handle without its second layout; no exception comes out.
+void creation_without_memory() {
+    const Csr jag = banded(62'000, 62'000, 0);
+    Csr rest = banded(4'000, 4'000, 0);  // rows cut to the k-vector product's tiles, and a long row
+    for (int k = 0; k < 5000; ++k) rest.col.push_back(k % 4000);
+    rest.end_row();
+    spmv_params wide{};
+    wide.tile_nnz = 4096;
+    for (const Csr *A : {&jag, (const Csr *)&rest}) {
+        const spmv_params *p = A == &jag ? nullptr : &wide;
+        int failed = 0, thrown = 0, other = 0, n = 1;
+        for (bool done = false; !done; ++n) {
+            spmv_matrix *M = nullptr;
+            int rc = SPMV_OK;
+            fail_at = n;
+            try {
+                rc = A->create(p, SPMV_VALUES_FP32, &M);
+            } catch (const std::exception &) {
+                ++thrown;
+                rc = SPMV_ENOMEM;
+            }
+            done = fail_at > 0;  // more than the creation makes
+            fail_at = 0;
+            if (rc == SPMV_ENOMEM) ++failed;
+            else if (rc != SPMV_OK) ++other;
+            if (rc != SPMV_OK && M) ++other;
+            if (M) spmv_destroy(M);
+        }
+        std::printf("  %d allocations, %d failed creations, %d exceptions\n", n - 2, failed, thrown);
+        check(failed > 0 && thrown == 0 && other == 0, "no exception leaves spmv_create");
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -262,6 +313,7 @@ int main(int argc, char **argv) {
     else if (what == "plans_without_gate") plans_without_gate();
     else if (what == "layout_memory") layout_memory();
     else if (what == "served_budget") served_budget();
+    else if (what == "creation_without_memory") creation_without_memory();
     else ++failures;
     return failures ? 1 : 0;
 }

@@ -63,3 +63,7 @@ def test_layouts_leave_half_of_the_memory_free(driver):
 
 def test_served_matrices_stay_within_the_bytes_counted_for_them(driver):
     run(driver, "served_budget")
+
+
+def test_creation_without_host_memory(driver):
+    run(driver, "creation_without_memory")
