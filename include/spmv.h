@@ -188,7 +188,7 @@ typedef struct spmv_info {
  * Device memory (spmv_info.device_bytes): 12 bytes per entry, 4 and 2 more
  * for FP32 and BF16 values, and the vectors of the plan.  A CSR-format handle
  * of 2^20 entries and more also keeps its entries in a second order where its
- * products are faster in it: about 1.6 bytes per entry and a copy of the
+ * products are faster in it: 2 to 3 bytes per entry and a copy of the
  * values (binary64 ones unless the plan has windows), or, for scattered
  * columns, 6 bytes per entry and a copy of the values.  It does so only while
  * half of the device's memory stays free, and not at all when tile_nnz,
